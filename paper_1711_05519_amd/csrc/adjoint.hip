@@ -38,10 +38,12 @@
 // combinations out = [panels] S with S formed by single-wave FP64 tails, and
 // the row-local Trim steps. Everything but D is FP64.
 
+#include <math.h>
 #include <string.h>
 
 #include "../../include/rpca.h"
 #include "launch.hpp"
+#include "train_pass.hpp"
 #include "wave.hpp"
 
 namespace rpca {
@@ -184,122 +186,6 @@ __global__ __launch_bounds__(256) void k_adj_trim(TrimArgs a, int reverse) {
     for (int t = 0; t < K; ++t) dot = fma(ab[t], x[t], dot);
     const double f = big ? c / (rho * rho * rho) * dot : 0.0;
     for (int t = 0; t < K; ++t) a.Xbar[side][(size_t)row * K + t] = fma(w, ab[t], -f * x[t]);
-}
-
-// ---- the pass over D ----------------------------------------------------------------
-//
-// Tile TM x 256, one thread per column. Per element: x = D - L_k, g, z = D - s(x),
-// and (reverse) zd = x g (1 - g) / tau, s' = g + |x| g (1 - g) / tau,
-// Zbar = Uz_i . Xz_j + Yz_i . Vz_j, h = Zbar s'. Row products
-// [z ro0_j | h ro1_j] are summed over the tile's columns (wave shuffles, then
-// the waves in order), column products [z co0_i | h co1_i] over its rows in
-// registers. Per tile: sum (x - s)^2 and sum Zbar zd.
-struct AdjStream {
-    const void* D;
-    int64_t ldd;
-    int32_t m, n, TM, n_ct, n_rt, hw;
-    const double* U;
-    const double* sig;
-    const double* V;
-    double zeta, tau;
-    PanelRef ro0, ro1, co0, co1;
-    PanelRef Uz, Yz, Xz, Vz;
-    double* Rp;       // [n_ct][m][WR]
-    double* Cp;       // [n_rt][n][WC]
-    double* scal;     // [tiles][2]
-};
-
-__device__ inline double logistic(double u) { return 0.5 * (1.0 + tanh(0.5 * u)); }
-
-template <typename T, int K, bool BWD>
-__global__ __launch_bounds__(RX_THREADS) void k_adj_stream(AdjStream a) {
-    constexpr int W2 = BWD ? 2 * K : 0;
-    constexpr int KZ = BWD ? K : 1;
-    const int WR = K + (BWD ? a.hw : 0);
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    const int ct = blockIdx.x % a.n_ct, rt = blockIdx.x / a.n_ct;
-    const int j = ct * RX_THREADS + threadIdx.x;
-    const bool valid = j < a.n;
-    const int i_lo = rt * a.TM, i_hi = min(a.m, i_lo + a.TM);
-    const T* __restrict__ D = static_cast<const T*>(a.D);
-    const double zeta = a.zeta, tau = a.tau;
-    double vb[K], ro[K + W2], acc[K + W2], xz[KZ], vz[KZ];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        vb[t] = valid ? a.V[(size_t)j * K + t] : 0.0;
-        ro[t] = valid ? a.ro0.p[(size_t)j * a.ro0.ld + t] : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < W2; ++t) ro[K + t] = (valid && t < a.hw) ? a.ro1.p[(size_t)j * a.ro1.ld + t] : 0.0;
-#pragma unroll
-    for (int t = 0; t < K + W2; ++t) acc[t] = 0.0;
-    if constexpr (BWD) {
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
-            xz[t] = valid ? a.Xz.p[(size_t)j * a.Xz.ld + t] : 0.0;
-            vz[t] = valid ? a.Vz.p[(size_t)j * a.Vz.ld + t] : 0.0;
-        }
-    }
-    __shared__ double red[RX_THREADS / WAVE][3 * RX_KMAX];
-    __shared__ double bred[RX_THREADS / WAVE];
-    double res = 0.0, zsum = 0.0;
-    for (int i = i_lo; i < i_hi; ++i) {
-        double x = valid ? static_cast<double>(D[(size_t)i * a.ldd + j]) : 0.0;
-        const double d = x;
-#pragma unroll
-        for (int t = 0; t < K; ++t) x = fma(-(a.U[(size_t)i * K + t] * a.sig[t]), vb[t], x);
-        const double g = logistic((fabs(x) - zeta) / tau);
-        const double s = x * g;
-        const double z = valid ? d - s : 0.0;
-        double h = 0.0;
-        if (valid) res = fma(x - s, x - s, res);
-        if constexpr (BWD) {
-            double zb = 0.0;
-#pragma unroll
-            for (int t = 0; t < K; ++t) {
-                zb = fma(a.Uz.p[(size_t)i * a.Uz.ld + t], xz[t], zb);
-                zb = fma(a.Yz.p[(size_t)i * a.Yz.ld + t], vz[t], zb);
-            }
-            const double gg = g * (1.0 - g) / tau;
-            if (valid) {
-                zsum = fma(zb, x * gg, zsum);
-                h = zb * fma(fabs(x), gg, g);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < K; ++t) acc[t] = fma(z, a.co0.p[(size_t)i * a.co0.ld + t], acc[t]);
-        if constexpr (BWD) {
-#pragma unroll
-            for (int t = 0; t < W2; ++t)
-                if (t < a.hw) acc[K + t] = fma(h, a.co1.p[(size_t)i * a.co1.ld + t], acc[K + t]);
-        }
-#pragma unroll
-        for (int t = 0; t < K + W2; ++t) {
-            if (t < WR) {
-                double v = (t < K ? z : h) * ro[t];
-                for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-                if (lane == 0) red[wave][t] = v;
-            }
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < WR) {
-            double v = 0.0;
-            for (int w = 0; w < RX_THREADS / WAVE; ++w) v += red[w][threadIdx.x];
-            a.Rp[((size_t)ct * a.m + i) * WR + threadIdx.x] = v;
-        }
-        __syncthreads();
-    }
-    if (valid) {
-#pragma unroll
-        for (int t = 0; t < K + W2; ++t)
-            if (t < WR) a.Cp[((size_t)rt * a.n + j) * WR + t] = acc[t];
-    }
-    const double r1 = block_sum(res, bred);
-    const double r2 = block_sum(zsum, bred);
-    if (threadIdx.x == 0) {
-        a.scal[2 * blockIdx.x] = r1;
-        a.scal[2 * blockIdx.x + 1] = r2;
-    }
 }
 
 // Sums of the pass's tile partials, in tile order: SR = sum_ct Rp (m x W),
@@ -786,13 +672,13 @@ struct Host {
     }
 
     template <typename T>
-    hipError_t stream_t(const AdjStream& a, bool bwd) const {
-        const dim3 grid((unsigned)(a.n_ct * a.n_rt)), block(RX_THREADS);
+    hipError_t stream_t(const TrainPass<double>& a, bool bwd) const {
+        const dim3 grid((unsigned)(a.n_ct * a.n_rt)), block(TP_THREADS);
         switch (K) {
-#define RPCA_CASE(KK)                                                                                   \
-    case KK:                                                                                            \
-        if (bwd) hipLaunchKernelGGL((k_adj_stream<T, KK, true>), grid, block, 0, s, a);                \
-        else hipLaunchKernelGGL((k_adj_stream<T, KK, false>), grid, block, 0, s, a);                    \
+#define RPCA_CASE(KK)                                                                                             \
+    case KK:                                                                                                      \
+        if (bwd) hipLaunchKernelGGL((k_train_pass<T, double, KK, TRAIN_REVERSE>), grid, block, 0, s, a);         \
+        else hipLaunchKernelGGL((k_train_pass<T, double, KK, TRAIN_RECOMPUTE>), grid, block, 0, s, a);            \
         break;
             RPCA_CASE(1) RPCA_CASE(2) RPCA_CASE(3) RPCA_CASE(4) RPCA_CASE(5)
             RPCA_CASE(6) RPCA_CASE(7) RPCA_CASE(8) RPCA_CASE(9) RPCA_CASE(10)
@@ -803,7 +689,7 @@ struct Host {
     }
 
     // one pass over D at checkpoint k and its tile sums into SR (m x W) and SC (n x W)
-    hipError_t pass(int k, bool bwd, AdjStream a, int W, double* SR, double* SC, double* scal_out) const {
+    hipError_t pass(int k, bool bwd, TrainPass<double> a, int W, double* SR, double* SC, double* scal_out) const {
         a.D = P.D;
         a.ldd = P.ldd;
         a.m = m;
@@ -811,11 +697,11 @@ struct Host {
         a.TM = P.TM;
         a.n_ct = P.n_ct;
         a.n_rt = P.n_rt;
-        a.U = P.U[k];
+        a.Lr = {P.U[k], K};
+        a.Lc = {P.V[k], K};
         a.sig = P.sigma[k];
-        a.V = P.V[k];
         a.zeta = P.zeta[k];
-        a.tau = P.tau[k];
+        a.itau = fmin(1.0 / P.tau[k], DBL_MAX);
         a.Rp = B.Rp;
         a.Cp = B.Cp;
         a.scal = B.scal;
@@ -874,11 +760,10 @@ struct Host {
         // U~ = A R_A^{-1} into the first K columns of B_U (row stride 2K)
         if ((e = combine(a1, 1, S.RAinv, K, S.BU, N, b1, 1, S.RBinv, K, S.BV, N)) != hipSuccess) return e;
         // Y1 = Z V~, Y2 = Z^T U~
-        AdjStream a;
+        TrainPass<double> a;
         memset(&a, 0, sizeof(a));
-        a.ro0 = pr(S.BV, N, K);
-        a.co0 = pr(S.BU, N, K);
-        a.hw = 0;
+        a.c0 = {S.BV, N};
+        a.r0 = {S.BU, N};
         if ((e = pass(k, false, a, K, B.Y1, B.Y2, B.scal_out)) != hipSuccess) return e;
         PanelRef ut[1] = {pr(S.BU, N, K)}, vt[1] = {pr(S.BV, N, K)};
         PanelRef y1[1] = {pr(B.Y1, K, K)}, y2[1] = {pr(B.Y2, K, K)};
@@ -1046,23 +931,23 @@ hipError_t adjoint_run(const AdjointProblem& P, const AdjointBufs& B, hipStream_
         // the previous body's bases (its forward recompute) for the Hadamard products
         if (k >= 1 && (e = h.forward(k - 1, sl ^ 1)) != hipSuccess) return e;
         // pass over D at L_k: Z N_V | h B_V', Z^T N_U | h B_U', dloss/dzeta_k
-        AdjStream a;
+        TrainPass<double> a;
         memset(&a, 0, sizeof(a));
-        a.ro0 = pr(B.XG + K, 3 * K, K);         // N_V
-        a.co0 = pr(B.YG, N, K);                 // N_U = Y_
+        a.c0 = {B.XG + K, 3 * K};               // N_V
+        a.r0 = {B.YG, N};                       // N_U = Y_
         if (k >= 1) {
             a.hw = N;
-            a.ro1 = pr(Sp.BV, N, N);
-            a.co1 = pr(Sp.BU, N, N);
+            a.c1 = {Sp.BV, N};
+            a.r1 = {Sp.BU, N};
         } else {
             a.hw = K;
-            a.ro1 = pr(P.V[0], K, K);
-            a.co1 = pr(P.U[0], K, K);
+            a.c1 = {P.V[0], K};
+            a.r1 = {P.U[0], K};
         }
-        a.Uz = pr(S.BU, N, K);
-        a.Vz = pr(S.BV, N, K);
-        a.Xz = pr(B.XG, 3 * K, K);
-        a.Yz = pr(B.YG, N, K);
+        a.Uz = {S.BU, N};
+        a.Vz = {S.BV, N};
+        a.Xz = {B.XG, 3 * K};
+        a.Yz = {B.YG, N};
         const int W = K + a.hw;
         if ((e = h.pass(k, true, a, W, B.SR, B.SC, B.scal_out + 2 * 0)) != hipSuccess) return e;
         if ((e = hipMemcpyAsync(P.zeta_bar_dev + k, B.scal_out + 1, sizeof(double), hipMemcpyDeviceToDevice, s)) !=

@@ -369,12 +369,13 @@ Layout make_layout(const rpca_params* p) {
         L.rx_nct = (n + RX_THREADS - 1) / RX_THREADS;
         int nrt = (m + 63) / 64;
         if (nrt > RX_MAX_RT) nrt = RX_MAX_RT;
-        L.rx_TM = (m + nrt - 1) / nrt;
+        L.rx_TM = (int)align_up((size_t)((m + nrt - 1) / nrt), 16);   // whole 16-row blocks
         L.rx_nrt = (m + L.rx_TM - 1) / L.rx_TM;
         const int gp = (m + 255) / 256 + (n + 255) / 256;
+        const size_t scratch0 = off;
         L.off_R1 = take(sizeof(double) * (size_t)L.rx_nct * m * K2);
         L.off_R2 = take(sizeof(double) * (size_t)L.rx_nrt * n * K2);
-        L.off_Rres = take(sizeof(double) * (size_t)L.rx_nct * L.rx_nrt);
+        L.off_Rres = take(2 * sizeof(double) * (size_t)L.rx_nct * L.rx_nrt);
         L.off_RY1 = take(sizeof(double) * (size_t)m * K2);
         L.off_RY2 = take(sizeof(double) * (size_t)n * K2);
         L.off_gpR = take(sizeof(double) * (size_t)gp * RX_WMAX * RX_WMAX);
@@ -382,7 +383,12 @@ Layout make_layout(const rpca_params* p) {
         L.off_gram2 = take(sizeof(double) * 2 * RX_WMAX * RX_WMAX);
         L.off_coef = take(sizeof(double) * 6 * KMAX * KMAX);
         L.off_rres = take(sizeof(RelaxResult));
+        // the reverse sweep shares the forward step's memory: neither keeps
+        // anything there from one call to the next
+        const size_t forward_end = off;
+        off = scratch0;
         L.off_adj = take(adjoint_ws_bytes(m, n, p->r, L.rx_nct, L.rx_nrt));
+        if (off < forward_end) off = forward_end;
     }
     L.total = off;
     return L;

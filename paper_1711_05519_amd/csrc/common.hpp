@@ -32,8 +32,8 @@ constexpr int GPART_STRIDE = 2 * KMAX * KMAX;   // doubles per workgroup partial
 // relaxed iteration (threshold training)
 constexpr int RX_KMAX = 10;        // largest rank of the relaxed iteration (3r <= 30 for the wave SVD)
 constexpr int RX_TRUE_MAX = 16;    // largest rank of the loss's target factors
-constexpr int RX_THREADS = 256;    // columns per tile of its pass over D (one per thread)
-constexpr int RX_MAX_RT = 16;      // row tiles of that pass
+constexpr int RX_THREADS = 256;    // columns per tile of its pass over D
+constexpr int RX_MAX_RT = 32;      // row tiles of that pass: 256 tiles, one per CU, at m = n = 2000
 constexpr int RX_WMAX = 3 * RX_KMAX + RX_TRUE_MAX;   // widest Gram, [F Y dY P]
 // threshold network: phi (4) -> 32 -> 32 -> 1
 constexpr int MLP_IN = 4, MLP_H = 32;

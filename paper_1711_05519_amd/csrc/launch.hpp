@@ -109,7 +109,7 @@ struct RelaxArgs {
     const void* AL; const void* BL; const void* Uf; const void* Vf;
     double zeta, tau, normD2;
     int32_t TM, n_ct, n_rt, n_tiles, gU, gV;
-    double* R1; double* R2; double* Rres;   // per-tile partials [n_ct][m][2K], [n_rt][n][2K]
+    double* R1; double* R2; double* Rres;   // per-tile partials [n_ct][m][2K], [n_rt][n][2K], [tiles][2]
     double* RY1; double* RY2;               // [Y1 dY1] (m x 2K), [Y2 dY2] (n x 2K)
     double* gpartR;                         // Gram partials
     double* gram;  double* gram2;           // [F Y dY P] and [W dW P] Grams, U side then V side

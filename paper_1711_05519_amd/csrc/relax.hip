@@ -27,93 +27,17 @@
 // exact Grams with the target factors; a single-wave FP64 tail with the
 // small algebra; and the row update of the new factors.
 
+#include <math.h>
+#include <string.h>
+
 #include "launch.hpp"
+#include "train_pass.hpp"
 #include "wave.hpp"
 
 namespace rpca {
 namespace {
 
-template <typename T> __device__ inline const T* cptr(const void* p) { return static_cast<const T*>(p); }
-
-__device__ inline double logistic(double u) { return 0.5 * (1.0 + tanh(0.5 * u)); }
-
-// ---- the pass over D -----------------------------------------------------------
-//
-// Tile RX_TM x 256: one thread per column; per row the 2K row products are
-// summed over the workgroup (wave shuffles, then LDS in wave order).
-template <typename T, int K>
-__global__ __launch_bounds__(RX_THREADS) void k_relax_stream(RelaxArgs a) {
-    constexpr int K2 = 2 * K;
-    const T* __restrict__ D = cptr<T>(a.D);
-    const T* __restrict__ AL = cptr<T>(a.AL);
-    const T* __restrict__ BL = cptr<T>(a.BL);
-    const T* __restrict__ Uf = cptr<T>(a.Uf);
-    const T* __restrict__ Vf = cptr<T>(a.Vf);
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    const int ct = blockIdx.x % a.n_ct, rt = blockIdx.x / a.n_ct;
-    const int j = ct * RX_THREADS + threadIdx.x;
-    const bool valid = j < a.n;
-    const int i_lo = rt * a.TM, i_hi = min(a.m, i_lo + a.TM);
-    const double zeta = a.zeta, tau = a.tau;
-    double bl[K], vt[K], y2[K2];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        bl[t] = valid ? static_cast<double>(BL[(size_t)j * K + t]) : 0.0;
-        vt[t] = valid ? static_cast<double>(Vf[(size_t)j * K + t]) : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < K2; ++t) y2[t] = 0.0;
-    __shared__ double red[RX_THREADS / WAVE][K2];
-    __shared__ double bred[RX_THREADS / WAVE];
-    double res = 0.0;
-    for (int i = i_lo; i < i_hi; ++i) {
-        double p[K2];
-        double x = valid ? static_cast<double>(D[(size_t)i * a.ldd + j]) : 0.0;
-        const double d = x;
-#pragma unroll
-        for (int t = 0; t < K; ++t) x -= static_cast<double>(AL[(size_t)i * K + t]) * bl[t];
-        double z = 0.0, zd = 0.0;
-        if (valid) {
-            const double g = logistic((fabs(x) - zeta) / tau);
-            const double s = x * g;
-            z = d - s;
-            zd = x * g * (1.0 - g) / tau;   // dZ/dzeta = -ds/dzeta
-            const double e = x - s;
-            res = fma(e, e, res);
-        }
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
-            const double u = static_cast<double>(Uf[(size_t)i * K + t]);
-            y2[t] = fma(z, u, y2[t]);
-            y2[K + t] = fma(zd, u, y2[K + t]);
-            p[t] = z * vt[t];
-            p[K + t] = zd * vt[t];
-        }
-#pragma unroll
-        for (int t = 0; t < K2; ++t) {
-            double v = p[t];
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-            p[t] = v;
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int t = 0; t < K2; ++t) red[wave][t] = p[t];
-        }
-        __syncthreads();
-        if (threadIdx.x < K2) {
-            double v = 0.0;
-            for (int w = 0; w < RX_THREADS / WAVE; ++w) v += red[w][threadIdx.x];
-            a.R1[((size_t)ct * a.m + i) * K2 + threadIdx.x] = v;
-        }
-        __syncthreads();
-    }
-    if (valid) {
-#pragma unroll
-        for (int t = 0; t < K2; ++t) a.R2[((size_t)rt * a.n + j) * K2 + t] = y2[t];
-    }
-    const double tot = block_sum(res, bred);
-    if (threadIdx.x == 0) a.Rres[blockIdx.x] = tot;
-}
+template <typename T> __host__ __device__ inline const T* cptr(const void* p) { return static_cast<const T*>(p); }
 
 // ---- sums over the tiles --------------------------------------------------------
 template <int K>
@@ -431,7 +355,10 @@ __global__ __launch_bounds__(WAVE) void k_relax_tail(RelaxArgs a) {
         hdh = fma(Hm[e], Hd[e], hdh);
         hdpq = fma(Hd[e], PQ[e], hdpq);
     }
+    double rs = 0.0;   // the relaxed residual, in tile order per lane
+    for (int b = lane; b < a.n_tiles; b += WAVE) rs += a.Rres[2 * b];
     for (int off = 32; off > 0; off >>= 1) {
+        rs += __shfl_xor(rs, off, WAVE);
         acc += __shfl_xor(acc, off, WAVE);
         h2 += __shfl_xor(h2, off, WAVE);
         hpq += __shfl_xor(hpq, off, WAVE);
@@ -463,8 +390,6 @@ __global__ __launch_bounds__(WAVE) void k_relax_tail(RelaxArgs a) {
     for (int e = lane; e < 6 * K * K; e += WAVE) a.coef[e] = out6[e];
     if (lane < K) a.sigma_out[lane] = sg[lane];
     if (lane == 0) {
-        double rs = 0.0;
-        for (int b = 0; b < a.n_tiles; ++b) rs += a.Rres[b];
         RelaxResult r;
         r.loss = (h2 - 2.0 * hpq + acc) / acc;
         r.dloss_dzeta = 2.0 * (hdh - hdpq) / acc;
@@ -511,13 +436,31 @@ __global__ __launch_bounds__(256) void k_relax_update(RelaxArgs a) {
 
 template <typename T>
 hipError_t relax_dispatch(const RelaxArgs& a, hipStream_t s) {
+    TrainPass<T> tp;
+    memset(&tp, 0, sizeof(tp));
+    tp.D = a.D;
+    tp.ldd = a.ldd;
+    tp.m = a.m;
+    tp.n = a.n;
+    tp.TM = a.TM;
+    tp.n_ct = a.n_ct;
+    tp.n_rt = a.n_rt;
+    tp.zeta = a.zeta;
+    tp.itau = fmin(1.0 / a.tau, DBL_MAX);
+    tp.Lr = {cptr<T>(a.AL), a.K};
+    tp.Lc = {cptr<T>(a.BL), a.K};
+    tp.r0 = {cptr<T>(a.Uf), a.K};
+    tp.c0 = {cptr<T>(a.Vf), a.K};
+    tp.Rp = a.R1;
+    tp.Cp = a.R2;
+    tp.scal = a.Rres;
     const unsigned gs = (unsigned)(a.n_ct * a.n_rt);
     const unsigned gsum = (unsigned)((((int64_t)a.m + a.n) * 2 * a.K + 255) / 256);
     const unsigned gpan = (unsigned)(a.gU + a.gV);
     switch (a.K) {
 #define RPCA_CASE(KK)                                                                            \
     case KK:                                                                                     \
-        hipLaunchKernelGGL((k_relax_stream<T, KK>), dim3(gs), dim3(RX_THREADS), 0, s, a);       \
+        hipLaunchKernelGGL((k_train_pass<T, T, KK, TRAIN_STEP>), dim3(gs), dim3(TP_THREADS), 0, s, tp); \
         hipLaunchKernelGGL((k_relax_sum<KK>), dim3(gsum), dim3(256), 0, s, a);                   \
         hipLaunchKernelGGL((k_relax_gram<T, KK, true>), dim3(gpan), dim3(256), 0, s, a, (int)CNT_RELAX, a.gram);  \
         hipLaunchKernelGGL((k_relax_complement<T, KK>), dim3(gpan), dim3(256), 0, s, a);          \
