@@ -371,14 +371,13 @@ Layout make_layout(const rpca_params* p) {
         if (nrt > RX_MAX_RT) nrt = RX_MAX_RT;
         L.rx_TM = (int)align_up((size_t)((m + nrt - 1) / nrt), 16);   // whole 16-row blocks
         L.rx_nrt = (m + L.rx_TM - 1) / L.rx_TM;
-        const int gp = (m + 255) / 256 + (n + 255) / 256;
         const size_t scratch0 = off;
         L.off_R1 = take(sizeof(double) * (size_t)L.rx_nct * m * K2);
         L.off_R2 = take(sizeof(double) * (size_t)L.rx_nrt * n * K2);
         L.off_Rres = take(2 * sizeof(double) * (size_t)L.rx_nct * L.rx_nrt);
         L.off_RY1 = take(sizeof(double) * (size_t)m * K2);
         L.off_RY2 = take(sizeof(double) * (size_t)n * K2);
-        L.off_gpR = take(sizeof(double) * (size_t)gp * RX_WMAX * RX_WMAX);
+        L.off_gpR = take(sizeof(double) * train_gpart_doubles(m, n));
         L.off_gram = take(sizeof(double) * 2 * RX_WMAX * RX_WMAX);
         L.off_gram2 = take(sizeof(double) * 2 * RX_WMAX * RX_WMAX);
         L.off_coef = take(sizeof(double) * 6 * KMAX * KMAX);
@@ -1454,8 +1453,6 @@ int rpca_relaxed_step(const void* D, const rpca_params* p, rpca_state* st, doubl
     a.n_ct = L.rx_nct;
     a.n_rt = L.rx_nrt;
     a.n_tiles = L.rx_nct * L.rx_nrt;
-    a.gU = (a.m + 255) / 256;
-    a.gV = (a.n + 255) / 256;
     a.R1 = c.at<double>(L.off_R1);
     a.R2 = c.at<double>(L.off_R2);
     a.Rres = c.at<double>(L.off_Rres);

@@ -35,6 +35,21 @@ constexpr int RX_TRUE_MAX = 16;    // largest rank of the loss's target factors
 constexpr int RX_THREADS = 256;    // columns per tile of its pass over D
 constexpr int RX_MAX_RT = 32;      // row tiles of that pass: 256 tiles, one per CU, at m = n = 2000
 constexpr int RX_WMAX = 3 * RX_KMAX + RX_TRUE_MAX;   // widest Gram, [F Y dY P]
+// panel steps of the relaxed iterations (train_panel.hpp)
+constexpr int TR_THREADS = 256;
+constexpr int TR_WAVES = TR_THREADS / WAVE;
+constexpr int TR_ROWS = 16 * TR_WAVES;   // rows of a workgroup at a time
+constexpr int TR_MAX_BLK = 64;           // workgroups per side, each looping over its rows: the last
+                                         // workgroup sums the Gram partials of all of them
+constexpr int TR_GE = 2048;              // entries of a Gram partial (and of a small-matrix slot)
+__host__ __device__ constexpr int train_rows_per_block(int64_t rows) {
+    const int64_t units = (rows + TR_ROWS - 1) / TR_ROWS;
+    return (int)((units + TR_MAX_BLK - 1) / TR_MAX_BLK) * TR_ROWS;
+}
+__host__ __device__ constexpr size_t train_gpart_doubles(int64_t m, int64_t n) {
+    return (size_t)((m + train_rows_per_block(m) - 1) / train_rows_per_block(m) +
+                    (n + train_rows_per_block(n) - 1) / train_rows_per_block(n)) * TR_GE;
+}
 // threshold network: phi (4) -> 32 -> 32 -> 1
 constexpr int MLP_IN = 4, MLP_H = 32;
 constexpr int MLP_PARAMS = MLP_H * MLP_IN + MLP_H + MLP_H * MLP_H + MLP_H + MLP_H + 1;   // 1249

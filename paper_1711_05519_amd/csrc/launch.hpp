@@ -108,14 +108,14 @@ struct RelaxArgs {
     int32_t m, n, K, rt_true;
     const void* AL; const void* BL; const void* Uf; const void* Vf;
     double zeta, tau, normD2;
-    int32_t TM, n_ct, n_rt, n_tiles, gU, gV;
+    int32_t TM, n_ct, n_rt, n_tiles;
     double* R1; double* R2; double* Rres;   // per-tile partials [n_ct][m][2K], [n_rt][n][2K], [tiles][2]
     double* RY1; double* RY2;               // [Y1 dY1] (m x 2K), [Y2 dY2] (n x 2K)
     double* gpartR;                         // Gram partials
-    double* gram;  double* gram2;           // [F Y dY P] and [W dW P] Grams, U side then V side
+    double* gram;  double* gram2;           // [F P]^T [Y dY P] and [W dW]^T [W dW P], U side then V side
     const double* P; const double* Q;       // target factors, m x rt_true and n x rt_true
     const double* RUinv; const double* RVinv;
-    double* coef;                           // 6 K x K coefficient blocks of the new factors
+    double* coef;                           // coefficients of the panel steps, and C, dC
     double* sigma_out; double* Uout; double* Vout;
     RelaxResult* result;
     Ctrl* ctrl;
@@ -168,12 +168,12 @@ struct AdjointProblem {
 };
 struct AdjointBufs {
     struct Slot {
-        double *Am, *wU, *rhoU, *BU, *Bm, *wV, *rhoV, *BV;
+        double *Am, *BU, *Bm, *BV;
         double *RAinv, *RBinv, *C, *R1, *R2, *R1inv, *R2inv, *UM, *SM, *VM;
     } slot[2];
-    double *Y1, *W1, *GammaV, *YG, *SR, *GU, *Abar, *Utrim, *F1;
-    double *Y2, *W2, *GammaU, *XG, *SC, *GV, *Bbar, *Vtrim, *F2;
-    double *Rp, *Cp, *scal, *scal_out, *gpart, *small;
+    double *Y1, *W1, *GammaV, *YG, *SR, *GU, *Utrim, *F1;
+    double *Y2, *W2, *GammaU, *XG, *SC, *GV, *Vtrim, *F2;
+    double *Rp, *Cp, *scal, *gpart, *small;
     double* zbar;                             // dloss/dzeta_k, RPCA_MAX_UNROLL values
     uint32_t* cnt;
     char* end;

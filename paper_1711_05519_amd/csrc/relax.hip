@@ -20,422 +20,281 @@
 // projections of P and Q onto B_U and B_V.
 //
 // Kernels: one pass over D giving [Y1 dY1] = [Z dZ] V_f and [Y2 dY2] = [Z dZ]^T U_f
-// as per-tile partials (plus the relaxed residual); their sums; the products
-// [U_f | Y1 dY1 | P]^T [...] (for C, dC and U*^T P); the explicit complements
+// as per-tile partials (plus the relaxed residual; train_pass.hpp), then three
+// panel steps (train_panel.hpp): the sums over the tiles with the products
+// [U_f | P]^T [Y1 dY1 | P] (for C, dC and U*^T P); the explicit complements
 // [W1 dW1] = [Y1 dY1] R_V^{-1} - U* [C dC] (and the V side), formed row by row
-// in FP64 as the FP64 loop path does (Gram differences would cancel); their
-// exact Grams with the target factors; a single-wave FP64 tail with the
-// small algebra; and the row update of the new factors.
+// in FP64 as the FP64 loop path does (Gram differences would cancel), with
+// their exact Grams and the small FP64 algebra; and the new factors.
 
 #include <math.h>
 #include <string.h>
 
+#include <initializer_list>
+
 #include "launch.hpp"
+#include "train_panel.hpp"
 #include "train_pass.hpp"
 #include "wave.hpp"
 
 namespace rpca {
 namespace {
 
-template <typename T> __host__ __device__ inline const T* cptr(const void* p) { return static_cast<const T*>(p); }
+template <typename T> inline const T* cptr(const void* p) { return static_cast<const T*>(p); }
 
-// ---- sums over the tiles --------------------------------------------------------
-template <int K>
-__global__ __launch_bounds__(256) void k_relax_sum(RelaxArgs a) {
-    constexpr int K2 = 2 * K;
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t mU = (int64_t)a.m * K2, mV = (int64_t)a.n * K2;
-    if (e < mU) {
-        double v = 0.0;
-        for (int c = 0; c < a.n_ct; ++c) v += a.R1[(size_t)c * mU + e];
-        a.RY1[e] = v;
-    } else if (e < mU + mV) {
-        const int64_t f = e - mU;
-        double v = 0.0;
-        for (int r = 0; r < a.n_rt; ++r) v += a.R2[(size_t)r * mV + f];
-        a.RY2[f] = v;
-    }
-}
+struct RelaxTailArgs {
+    int32_t stage, rt;            // 1: after the first Grams, 2: after the second
+    const double* G1[2];          // [F | P]^T [Y dY | P], (K + rt) x (2K + rt), U side and V side
+    const double* G2[2];          // [W dW]^T [W dW | P], 2K x (2K + rt)
+    const double* Rinv[2];        // R_U^{-1}, R_V^{-1} (row stride KMAX)
+    double* S[2];                 // stage 1: coefficients of the complements (3K x 2K); stage 2: of the factors (3K x K)
+    double* C;                    // C, then dC (K x K each)
+    const double* scal;           // per-tile residuals of the pass (pairs)
+    int32_t tiles;
+    double normD2;
+    double* sigma_out;
+    RelaxResult* result;
+};
 
-// ---- Grams of [F | Y | P] (WITH_F) or [Y | P] over the rows of each side ----------
-//
-// The first gU workgroups take rows of the U side (F = U_f, Y = the 2K-wide
-// panel RY1, P), the next gV rows of the V side (V_f, RY2, Q). Each writes the
-// W x W partial Gram of its 256 rows; the last workgroup sums them in order
-// into gram (U side) and gram + RX_WMAX^2 (V side), upper and lower halves.
-template <typename T, int K, bool WITH_F>
-__global__ __launch_bounds__(256) void k_relax_gram(RelaxArgs a, int cnt_slot, double* gram) {
-    constexpr int K2 = 2 * K;
-    constexpr int NF = WITH_F ? K : 0;
-    const int W = NF + K2 + a.rt_true;
-    const bool uside = (int)blockIdx.x < a.gU;
-    const int row = (uside ? blockIdx.x : blockIdx.x - a.gU) * 256 + threadIdx.x;
-    const int nrows = uside ? a.m : a.n;
-    const T* F = cptr<T>(uside ? a.Uf : a.Vf);
-    const double* Y = uside ? a.RY1 : a.RY2;
-    const double* P = uside ? a.P : a.Q;
-    __shared__ double rows[256][RX_WMAX + 1];
-    for (int c = 0; c < W; ++c) {
-        double v = 0.0;
-        if (row < nrows) {
-            if (c < NF) v = static_cast<double>(F[(size_t)row * K + c]);
-            else if (c < NF + K2) v = Y[(size_t)row * K2 + (c - NF)];
-            else v = P[(size_t)row * a.rt_true + (c - NF - K2)];
-        }
-        rows[threadIdx.x][c] = v;
-    }
-    __syncthreads();
-    double* gp = a.gpartR + (size_t)blockIdx.x * RX_WMAX * RX_WMAX;
-    for (int e = threadIdx.x; e < W * W; e += 256) {
-        const int p = e / W, q = e % W;
-        double v = 0.0;
-        if (p <= q)
-            for (int r = 0; r < 256; ++r) v = fma(rows[r][p], rows[r][q], v);
-        gp[p * RX_WMAX + q] = v;
-    }
-    __shared__ int flag;
-    if (!last_block_arrives(&a.ctrl->cnt[cnt_slot], &flag)) return;
-    for (int e = threadIdx.x; e < 2 * W * W; e += 256) {
-        const int side = e / (W * W), pq = e % (W * W);
-        const int p = pq / W, q = pq % W;
-        const int first = side ? a.gU : 0, count = side ? a.gV : a.gU;
-        const int lo = p <= q ? p : q, hi = p <= q ? q : p;
-        double v = 0.0;
-        for (int b = 0; b < count; ++b) v += a.gpartR[(size_t)(first + b) * RX_WMAX * RX_WMAX + lo * RX_WMAX + hi];
-        gram[(size_t)side * RX_WMAX * RX_WMAX + p * RX_WMAX + q] = v;
-    }
-    if (threadIdx.x == 0) a.ctrl->cnt[cnt_slot] = 0;
-}
+// The small FP64 algebra, by the last workgroup of a panel step.
+template <int K> struct RelaxTail {
+    using Args = RelaxTailArgs;
+    static constexpr int K2 = 2 * K, K3 = 3 * K;
 
-// C = Ra^T (F^T Y_a) Rb and dC = Ra^T (F^T Y_b) Rb from the first Gram
-// (F columns 0..K-1, Y columns K..3K-1), lane- or thread-parallel over entries.
-template <int K>
-__device__ inline void relax_c(const double* G, const double* Ra, const double* Rb, double* Cc, double* Cd,
-                               double* tmp, int tid, int nth) {
-    for (int e = tid; e < 2 * K * K; e += nth) {
-        const int w = e / (K * K), i = (e / K) % K, j = e % K;
-        double v = 0.0;
-        for (int l = 0; l < K; ++l) v = fma(G[i * RX_WMAX + K + w * K + l], Rb[l * K + j], v);
-        tmp[e] = v;   // (F^T Y_w Rb)[i][j]
+    // C = Ra^T (F^T Y) Rb and dC = Ra^T (F^T dY) Rb; the complements' coefficients
+    // for [Y dY | F]: [W dW] = [Y dY] diag(Rb, Rb) - F Ra [C dC]
+    static __device__ __forceinline__ void stage1(const Args& a) {
+        __shared__ double ra[K * K], rb[K * K], g[2 * K * K], t[2 * K * K], c[2 * K * K];
+        const int tid = threadIdx.x;
+        const int wR = K2 + a.rt;
+        for (int side = 0; side < 2; ++side) {
+            for (int e = tid; e < K * K; e += TR_THREADS) {
+                ra[e] = a.Rinv[side][(e / K) * KMAX + e % K];
+                rb[e] = a.Rinv[1 - side][(e / K) * KMAX + e % K];
+            }
+            for (int e = tid; e < 2 * K * K; e += TR_THREADS) g[e] = a.G1[side][(e / K2) * wR + e % K2];   // K x 2K
+            __syncthreads();
+            for (int e = tid; e < 2 * K * K; e += TR_THREADS) {   // t = (F^T [Y dY]) diag(Rb, Rb)
+                const int i = e / K2, j = e % K2, w = j / K;
+                double v = 0.0;
+                for (int l = 0; l < K; ++l) v = fma(g[i * K2 + w * K + l], rb[l * K + j - w * K], v);
+                t[e] = v;
+            }
+            __syncthreads();
+            for (int e = tid; e < 2 * K * K; e += TR_THREADS) {   // c = Ra^T t
+                const int i = e / K2, j = e % K2;
+                double v = 0.0;
+                for (int l = 0; l < K; ++l) v = fma(ra[l * K + i], t[l * K2 + j], v);
+                c[e] = v;
+                if (side == 0) a.C[(j / K) * K * K + i * K + j % K] = v;
+            }
+            __syncthreads();
+            for (int e = tid; e < K3 * K2; e += TR_THREADS) {
+                const int r = e / K2, j = e % K2;
+                double v = 0.0;
+                if (r < K2) {
+                    if (r / K == j / K) v = rb[(r % K) * K + j % K];
+                } else {
+                    for (int l = 0; l < K; ++l) v = fma(ra[(r - K2) * K + l], c[l * K2 + j], v);
+                    v = -v;
+                }
+                a.S[side][e] = v;
+            }
+            __syncthreads();
+        }
     }
-    __syncthreads();
-    for (int e = tid; e < 2 * K * K; e += nth) {
-        const int w = e / (K * K), i = (e / K) % K, j = e % K;
-        double v = 0.0;
-        for (int l = 0; l < K; ++l) v = fma(Ra[l * K + i], tmp[w * K * K + l * K + j], v);
-        (w ? Cd : Cc)[i * K + j] = v;
-    }
-    __syncthreads();
-}
 
-// ---- explicit complements, in place of the 2K-wide panels -----------------------
-// U side: [W1 dW1] = [Y1 dY1] R_V^{-1} - (U_f R_U^{-1}) [C dC]
-// V side: [W2 dW2] = [Y2 dY2] R_U^{-1} - (V_f R_V^{-1}) [C2 dC2]
-template <typename T, int K>
-__global__ __launch_bounds__(256) void k_relax_complement(RelaxArgs a) {
-    constexpr int K2 = 2 * K;
-    const bool uside = (int)blockIdx.x < a.gU;
-    const int row = (uside ? blockIdx.x : blockIdx.x - a.gU) * 256 + threadIdx.x;
-    const int nrows = uside ? a.m : a.n;
-    __shared__ double ra[K * K], rb[K * K], cc[K * K], cd[K * K], tmp[2 * K * K];
-    const double* RA = uside ? a.RUinv : a.RVinv;   // basis side
-    const double* RB = uside ? a.RVinv : a.RUinv;   // product side
-    for (int e = threadIdx.x; e < K * K; e += 256) {
-        ra[e] = RA[(e / K) * KMAX + e % K];
-        rb[e] = RB[(e / K) * KMAX + e % K];
-    }
-    __syncthreads();
-    relax_c<K>(a.gram + (uside ? 0 : RX_WMAX * RX_WMAX), ra, rb, cc, cd, tmp, threadIdx.x, 256);
-    if (row >= nrows) return;
-    const T* F = cptr<T>(uside ? a.Uf : a.Vf);
-    double* Y = uside ? a.RY1 : a.RY2;
-    double f[K], fs[K], y[K2];
-#pragma unroll
-    for (int t = 0; t < K; ++t) f[t] = static_cast<double>(F[(size_t)row * K + t]);
-#pragma unroll
-    for (int t = 0; t < K2; ++t) y[t] = Y[(size_t)row * K2 + t];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        double v = 0.0;
-#pragma unroll
-        for (int l = 0; l < K; ++l) v = fma(f[l], ra[l * K + t], v);
-        fs[t] = v;   // row of U* (or V*)
-    }
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        double w = 0.0, wd = 0.0;
-#pragma unroll
-        for (int l = 0; l < K; ++l) {
-            w = fma(y[l], rb[l * K + t], w);
-            wd = fma(y[K + l], rb[l * K + t], wd);
-            w = fma(-fs[l], cc[l * K + t], w);
-            wd = fma(-fs[l], cd[l * K + t], wd);
+    // The reduced M and dM, the loss and its derivative, and the coefficients
+    // of the new factors.
+    //
+    // The Cholesky factors of the Grams of [W dW] are upper triangular, so the
+    // columns of M beyond 2K and its rows beyond 2K are zero: its SVD is that of the
+    // leading 2K x 2K block, completed by V_j = e_j and sigma_j = 0. Singular
+    // values at the rounding level are zero too, and their left vectors
+    // (undefined in the one-sided method) are dropped; the left null space
+    // then enters through a projector term (in the formula the block
+    // j >= rank, i < K, with F_ji = E_ji). The loss needs only inner products:
+    // <H, dH> = sum_i s_i F_ii, <H, P Q^T> and <dH, P Q^T> through the projections
+    // a = U_M^T B_U^T P and b = V_M^T B_V^T Q.
+    static __device__ __forceinline__ void stage2(const Args& a) {
+        constexpr int N = K2;
+        __shared__ double RG[2][K2 * K2], Ri[2][K2 * K2], GG[2][K2 * K2];
+        __shared__ double ra[2][K * K];
+        __shared__ double Mv[N * N], Um[N * N], Vm[N * N], sg[N];
+        __shared__ double dM[K3 * K3], A1[K3 * K], EL[N * K], A2[K * K3], ET[K * K3];
+        __shared__ double pr[2][K3 * RX_TRUE_MAX], ab[2][K3 * RX_TRUE_MAX];
+        __shared__ double red[TR_WAVES];
+        __shared__ int sweeps_s;
+        const int tid = threadIdx.x, rT = a.rt, wR = K2 + rT;
+        for (int e = tid; e < 2 * K2 * K2; e += TR_THREADS) {
+            const int side = e / (K2 * K2), i = e % (K2 * K2);
+            GG[side][i] = a.G2[side][(i / K2) * wR + i % K2];
         }
-        Y[(size_t)row * K2 + t] = w;
-        Y[(size_t)row * K2 + K + t] = wd;
-    }
-}
-
-// ---- the small FP64 algebra, one wave ---------------------------------------------
-
-template <int K>
-__global__ __launch_bounds__(WAVE) void k_relax_tail(RelaxArgs a) {
-    constexpr int K2 = 2 * K, K3 = 3 * K, N = (K3 + 1) / 2 * 2;
-    const int lane = lane_id();
-    const int rT = a.rt_true;
-    constexpr int LD = RX_WMAX;
-    // first Grams: [F | Y dY | P]; second: [W dW | P] (U side, then V side)
-    const double* G1u = a.gram;
-    const double* G1v = a.gram + LD * LD;
-    const double* G2u = a.gram2;
-    const double* G2v = a.gram2 + LD * LD;
-    __shared__ double ru[K * K], rv[K * K], tmp[2 * K * K], t1[K2 * RX_TRUE_MAX];
-    __shared__ double C[K * K], Cd[K * K], C2[K * K], C2d[K * K];
-    __shared__ double GG[K2 * K2], HH[K2 * K2], RG[K2 * K2], RGi[K2 * K2], RH[K2 * K2], RHi[K2 * K2];
-    __shared__ double Ma[N * N], Md[N * N], Mv[N * N], Um[N * N], Vm[N * N], sg[N], Ee[N * N], Fm[N * N];
-    __shared__ double Pr[K3 * RX_TRUE_MAX], Qr[K3 * RX_TRUE_MAX];
-    __shared__ double PQ[K3 * K3], Hm[K3 * K3], Hd[K3 * K3];
-    __shared__ double Z2[K2 * K], out6[6 * K * K];
-    for (int e = lane; e < K * K; e += WAVE) {
-        ru[e] = a.RUinv[(e / K) * KMAX + e % K];
-        rv[e] = a.RVinv[(e / K) * KMAX + e % K];
-    }
-    wave_sync();
-    relax_c<K>(G1u, ru, rv, C, Cd, tmp, lane, WAVE);
-    relax_c<K>(G1v, rv, ru, C2, C2d, tmp, lane, WAVE);
-    for (int e = lane; e < K2 * K2; e += WAVE) {
-        GG[e] = G2u[(e / K2) * LD + e % K2];
-        HH[e] = G2v[(e / K2) * LD + e % K2];
-    }
-    wave_sync();
-    w_chol_inv2<K2>(GG, RG, RGi, HH, RH, RHi);
-    // reduced M and dM (column-major, N x N, zero padded)
-    for (int e = lane; e < N * N; e += WAVE) {
-        const int col = e / N, row = e % N;
-        double m0 = 0.0, m1 = 0.0;
-        if (row < K && col < K) {
-            m0 = C[row * K + col];
-            m1 = Cd[row * K + col];
-        } else if (row < K && col < K3) {
-            m0 = RH[(col - K) * K2 + row];
-            m1 = RH[(col - K) * K2 + K + row];
-        } else if (row < K3 && col < K) {
-            m0 = RG[(row - K) * K2 + col];
-            m1 = RG[(row - K) * K2 + K + col];
+        for (int e = tid; e < 2 * K * K; e += TR_THREADS) {
+            const int side = e / (K * K), i = e % (K * K);
+            ra[side][i] = a.Rinv[side][(i / K) * KMAX + i % K];
         }
-        Ma[e] = m0;
-        Md[e] = m1;
-    }
-    wave_sync();
-    const int sweeps = wave_jacobi_svd<N, false>(Ma, Mv, sg, Um, Vm);   // Um, Vm column-major
-    // M has rank <= 2K: singular values at the rounding level are zero, and
-    // their left vectors (undefined in the one-sided method) are dropped; the
-    // left null space then enters through the projector term below.
-    {
-        const double cut = 1e-12 * sg[0];
-        for (int e = lane; e < N * N; e += WAVE)
-            if (sg[e / N] <= cut) Um[e] = 0.0;
-        wave_sync();
-        if (lane < N && sg[lane] <= cut) sg[lane] = 0.0;
-        wave_sync();
-    }
-    // E = U_M^T dM V_M (row-major N x N); dM column-major: element (r, c) = Md[c * N + r]
-    for (int e = lane; e < N * N; e += WAVE) {
-        const int i = e / N, j = e % N;
-        double v = 0.0;
-        for (int r = 0; r < N; ++r) {
-            double w = 0.0;
-            for (int c = 0; c < N; ++c) w = fma(Md[c * N + r], Vm[j * N + c], w);
-            v = fma(Um[i * N + r], w, v);
+        __syncthreads();
+        if (tid < WAVE) w_chol_inv2<K2>(GG[0], RG[0], Ri[0], GG[1], RG[1], Ri[1]);
+        __syncthreads();
+        // M (leading block, column-major, into GG[0], free now) and dM (row-major)
+        double* M = GG[0];
+        for (int e = tid; e < N * N; e += TR_THREADS) {
+            const int col = e / N, row = e % N;
+            double v = 0.0;
+            if (row < K && col < K) v = a.C[row * K + col];
+            else if (row < K) v = RG[1][(col - K) * K2 + row];
+            else if (col < K) v = RG[0][(row - K) * K2 + col];
+            M[e] = v;
         }
-        Ee[e] = v;
-    }
-    wave_sync();
-    for (int e = lane; e < N * N; e += WAVE) {
-        const int i = e / N, j = e % N;
-        double f = 0.0;
-        if (i < K && j < K) {
-            f = Ee[e];
-        } else if (i < K && j >= K) {
-            const double si = sg[i], sj = sg[j];
-            f = (si * si * Ee[i * N + j] + si * sj * Ee[j * N + i]) / (si * si - sj * sj);
-        } else if (j < K && i >= K) {
-            const double si = sg[j], sj = sg[i];
-            f = (si * si * Ee[i * N + j] + si * sj * Ee[j * N + i]) / (si * si - sj * sj);
+        for (int e = tid; e < K3 * K3; e += TR_THREADS) {
+            const int row = e / K3, col = e % K3;
+            double v = 0.0;
+            if (row < K && col < K) v = a.C[K * K + row * K + col];
+            else if (row < K) v = RG[1][(col - K) * K2 + K + row];
+            else if (col < K) v = RG[0][(row - K) * K2 + K + col];
+            dM[e] = v;
         }
-        Fm[e] = f;
-    }
-    wave_sync();
-    // H = U_M[:, :K] S_K V_M[:, :K]^T and dH = U_M F V_M^T on the leading K3 x K3 block
-    for (int e = lane; e < K3 * K3; e += WAVE) {
-        const int r = e / K3, c = e % K3;
-        double h = 0.0, hd = 0.0;
-        for (int t = 0; t < K; ++t) h = fma(Um[t * N + r] * sg[t], Vm[t * N + c], h);
-        for (int i = 0; i < N; ++i) {
-            double w = 0.0;
-            for (int j = 0; j < N; ++j) w = fma(Fm[i * N + j], Vm[j * N + c], w);
-            hd = fma(Um[i * N + r], w, hd);
+        // projections B_U^T P = [R_U^{-T} (U_f^T P) ; R_G^{-T} ([W1 dW1]^T P)], likewise B_V^T Q
+        for (int e = tid; e < 2 * K3 * rT; e += TR_THREADS) {
+            const int side = e / (K3 * rT), x = e % (K3 * rT), i = x / rT, q = x % rT;
+            double v = 0.0;
+            if (i < K) {
+                for (int l = 0; l < K; ++l) v = fma(ra[side][l * K + i], a.G1[side][l * wR + K2 + q], v);
+            } else {
+                for (int l = 0; l < K2; ++l) v = fma(Ri[side][l * K2 + i - K], a.G2[side][l * wR + K2 + q], v);
+            }
+            pr[side][i * rT + q] = v;
         }
-        Hm[e] = h;
-        Hd[e] = hd;
-    }
-    wave_sync();
-    // left-null-space part of the perturbation: (I - U_M U_M^T) dM V_K V_K^T
-    // (in the formula it is the block j >= rank, i < K, with F_ji = E_ji)
-    {
-        double* Tm = Ee;   // N x K, reuses Ee
-        for (int e = lane; e < N * K; e += WAVE) {
+        __syncthreads();
+        if (tid < WAVE) {
+            const int sweeps = wave_jacobi_svd<N, false>(M, Mv, sg, Um, Vm);   // Um, Vm column-major
+            const double cut = 1e-12 * sg[0];
+            for (int e = tid; e < N * N; e += WAVE)
+                if (sg[e / N] <= cut) Um[e] = 0.0;
+            wave_sync();
+            if (tid < N && sg[tid] <= cut) sg[tid] = 0.0;
+            if (tid == 0) sweeps_s = sweeps;
+        }
+        __syncthreads();
+        // A1 = dM V_K, A2 = U_K^T dM, a = U^T pr_U, b = V^T pr_V
+        for (int e = tid; e < K3 * K; e += TR_THREADS) {
             const int r = e / K, t = e % K;
             double v = 0.0;
-            for (int c = 0; c < N; ++c) v = fma(Md[c * N + r], Vm[t * N + c], v);
-            Tm[e] = v;
+            for (int c = 0; c < N; ++c) v = fma(dM[r * K3 + c], Vm[t * N + c], v);
+            A1[e] = v;
         }
-        wave_sync();
-        double* Pt = Fm;   // N x K, reuses Fm
-        for (int e = lane; e < N * K; e += WAVE) {
-            const int j = e / K, t = e % K;   // (U_M^T T)[j][t]
+        for (int e = tid; e < K * K3; e += TR_THREADS) {
+            const int i = e / K3, c = e % K3;
             double v = 0.0;
-            for (int r = 0; r < N; ++r) v = fma(Um[j * N + r], Tm[r * K + t], v);
-            Pt[e] = v;
+            for (int r = 0; r < N; ++r) v = fma(Um[i * N + r], dM[r * K3 + c], v);
+            A2[e] = v;
         }
-        wave_sync();
-        for (int e = lane; e < N * K; e += WAVE) {
-            const int r = e / K, t = e % K;
-            double v = Tm[e];
-            for (int j = 0; j < N; ++j) v -= Um[j * N + r] * Pt[j * K + t];
-            Md[e] = v;   // (I - U U^T) T, N x K, reuses Md
-        }
-        wave_sync();
-        for (int e = lane; e < K3 * K3; e += WAVE) {
-            const int r = e / K3, c = e % K3;
+        for (int e = tid; e < 2 * K3 * rT; e += TR_THREADS) {
+            const int side = e / (K3 * rT), x = e % (K3 * rT), j = x / rT, q = x % rT;
+            const double* X = side ? Vm : Um;
             double v = 0.0;
-            for (int t = 0; t < K; ++t) v = fma(Md[r * K + t], Vm[t * N + c], v);
-            Hd[e] += v;
+            if (j < N) {
+                for (int r = 0; r < N; ++r) v = fma(X[j * N + r], pr[side][r * rT + q], v);
+            } else if (side) {
+                v = pr[1][j * rT + q];
+            }
+            ab[side][j * rT + q] = v;
         }
-        wave_sync();
-    }
-    // projections of the target factors onto the reduced bases:
-    // B_U^T P = [R_U^{-T} (U_f^T P) ; R_G^{-T} ([W1 dW1]^T P)], likewise B_V^T Q
-    for (int side = 0; side < 2; ++side) {
-        const double* G1 = side ? G1v : G1u;
-        const double* G2 = side ? G2v : G2u;
-        const double* Ra = side ? rv : ru;
-        const double* Ri = side ? RHi : RGi;
-        double* Out = side ? Qr : Pr;
-        for (int e = lane; e < K * rT; e += WAVE) {
-            const int i = e / rT, q = e % rT;
-            double v = 0.0;
-            for (int l = 0; l < K; ++l) v = fma(Ra[l * K + i], G1[l * LD + K3 + q], v);
-            Out[e] = v;
-        }
-        for (int e = lane; e < K2 * rT; e += WAVE) t1[e] = G2[(e / rT) * LD + K2 + e % rT];
-        wave_sync();
-        for (int e = lane; e < K2 * rT; e += WAVE) {
-            const int i = e / rT, q = e % rT;
-            double v = 0.0;
-            for (int l = 0; l < K2; ++l) v = fma(Ri[l * K2 + i], t1[l * rT + q], v);
-            Out[K * rT + e] = v;
-        }
-        wave_sync();
-    }
-    for (int e = lane; e < K3 * K3; e += WAVE) {
-        const int i = e / K3, j = e % K3;
-        double v = 0.0;
-        for (int q = 0; q < rT; ++q) v = fma(Pr[i * rT + q], Qr[j * rT + q], v);
-        PQ[e] = v;
-    }
-    wave_sync();
-    // ||P Q^T||^2 = tr((P^T P)(Q^T Q)) and the inner products of the loss
-    double acc = 0.0, h2 = 0.0, hpq = 0.0, hdh = 0.0, hdpq = 0.0;
-    for (int e = lane; e < rT * rT; e += WAVE)
-        acc += G2u[(K2 + e / rT) * LD + K2 + e % rT] * G2v[(K2 + e / rT) * LD + K2 + e % rT];
-    for (int e = lane; e < K3 * K3; e += WAVE) {
-        h2 = fma(Hm[e], Hm[e], h2);
-        hpq = fma(Hm[e], PQ[e], hpq);
-        hdh = fma(Hm[e], Hd[e], hdh);
-        hdpq = fma(Hd[e], PQ[e], hdpq);
-    }
-    double rs = 0.0;   // the relaxed residual, in tile order per lane
-    for (int b = lane; b < a.n_tiles; b += WAVE) rs += a.Rres[2 * b];
-    for (int off = 32; off > 0; off >>= 1) {
-        rs += __shfl_xor(rs, off, WAVE);
-        acc += __shfl_xor(acc, off, WAVE);
-        h2 += __shfl_xor(h2, off, WAVE);
-        hpq += __shfl_xor(hpq, off, WAVE);
-        hdh += __shfl_xor(hdh, off, WAVE);
-        hdpq += __shfl_xor(hdpq, off, WAVE);
-    }
-    // new factors: U' = [U* Q] U_M[:, :K] = U_f (R_U^{-1} X1) + [W1 dW1] (R_G^{-1} X2)
-    for (int side = 0; side < 2; ++side) {
-        const double* Xm = side ? Vm : Um;
-        const double* Ri = side ? RHi : RGi;
-        const double* Ra = side ? rv : ru;
-        double* o = out6 + side * 3 * K * K;
-        for (int e = lane; e < K2 * K; e += WAVE) {
+        __syncthreads();
+        // E = U_M^T dM V_M where i < K or j < K: EL (columns j < K), ET (rows i < K)
+        for (int e = tid; e < N * K; e += TR_THREADS) {
             const int i = e / K, t = e % K;
             double v = 0.0;
-            for (int l = 0; l < K2; ++l) v = fma(Ri[i * K2 + l], Xm[t * N + K + l], v);
-            Z2[e] = v;
+            for (int r = 0; r < N; ++r) v = fma(Um[i * N + r], A1[r * K + t], v);
+            EL[e] = v;
         }
-        for (int e = lane; e < K * K; e += WAVE) {
-            const int i = e / K, t = e % K;
+        for (int e = tid; e < K * K3; e += TR_THREADS) {
+            const int i = e / K3, j = e % K3;
             double v = 0.0;
-            for (int l = 0; l < K; ++l) v = fma(Ra[i * K + l], Xm[t * N + l], v);
-            o[e] = v;
+            if (j < N) {
+                for (int c = 0; c < N; ++c) v = fma(A2[i * K3 + c], Vm[j * N + c], v);
+            } else {
+                v = A2[i * K3 + j];
+            }
+            ET[e] = v;
         }
-        wave_sync();
-        for (int e = lane; e < K2 * K; e += WAVE) o[K * K + e] = Z2[e];
-        wave_sync();
-    }
-    for (int e = lane; e < 6 * K * K; e += WAVE) a.coef[e] = out6[e];
-    if (lane < K) a.sigma_out[lane] = sg[lane];
-    if (lane == 0) {
-        RelaxResult r;
-        r.loss = (h2 - 2.0 * hpq + acc) / acc;
-        r.dloss_dzeta = 2.0 * (hdh - hdpq) / acc;
-        r.err = sqrt(rs / a.normD2);
-        r.sigma1 = sg[0];
-        r.sigma_r1 = sg[K];
-        r.sweeps = sweeps;
-        r.pad = 0;
-        *a.result = r;
-    }
-}
-
-// ---- row update of the new factors: U' = U_f E_F + [W1 dW1] [Za; Zb] ---------------
-template <typename T, int K>
-__global__ __launch_bounds__(256) void k_relax_update(RelaxArgs a) {
-    constexpr int K2 = 2 * K;
-    const bool uside = (int)blockIdx.x < a.gU;
-    const int row = (uside ? blockIdx.x : blockIdx.x - a.gU) * 256 + threadIdx.x;
-    const int nrows = uside ? a.m : a.n;
-    __shared__ double cf[3 * K * K];
-    for (int e = threadIdx.x; e < 3 * K * K; e += 256) cf[e] = a.coef[(uside ? 0 : 3 * K * K) + e];
-    __syncthreads();
-    if (row >= nrows) return;
-    const T* F = cptr<T>(uside ? a.Uf : a.Vf);
-    const double* Y = uside ? a.RY1 : a.RY2;
-    double f[K], y[K2];
-#pragma unroll
-    for (int t = 0; t < K; ++t) f[t] = static_cast<double>(F[(size_t)row * K + t]);
-#pragma unroll
-    for (int t = 0; t < K2; ++t) y[t] = Y[(size_t)row * K2 + t];
-    double* out = uside ? a.Uout : a.Vout;
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        double v = 0.0;
-#pragma unroll
-        for (int l = 0; l < K; ++l) {
-            v = fma(f[l], cf[l * K + t], v);
-            v = fma(y[l], cf[K * K + l * K + t], v);
-            v = fma(y[K + l], cf[2 * K * K + l * K + t], v);
+        __syncthreads();
+        double acc = 0.0, h2 = 0.0, hpq = 0.0, hdh = 0.0, hdpq = 0.0, rs = 0.0;
+        auto dot = [&](const double* x, const double* y) {
+            double v = 0.0;
+            for (int q = 0; q < rT; ++q) v = fma(x[q], y[q], v);
+            return v;
+        };
+        for (int b = tid; b < a.tiles; b += TR_THREADS) rs += a.scal[2 * b];   // the relaxed residual
+        for (int e = tid; e < rT * rT; e += TR_THREADS) {   // ||P Q^T||^2 = tr((P^T P)(Q^T Q))
+            const int at = (K + e / rT) * wR + K2 + e % rT;
+            acc = fma(a.G1[0][at], a.G1[1][at], acc);
         }
-        out[(size_t)row * K + t] = v;
+        for (int e = tid; e < K * K3; e += TR_THREADS) {
+            const int i = e / K3, j = e % K3;
+            const double si = sg[i];
+            if (j < K) {
+                const double f = ET[e];
+                hdpq = fma(f, dot(ab[0] + i * rT, ab[1] + j * rT), hdpq);
+                if (i == j) {
+                    hdh = fma(si, f, hdh);
+                    h2 = fma(si, si, h2);
+                    hpq = fma(si, dot(ab[0] + i * rT, ab[1] + i * rT), hpq);
+                }
+            } else {
+                const double sj = j < N ? sg[j] : 0.0, eij = ET[e], eji = j < N ? EL[j * K + i] : 0.0;
+                const double den = si * si - sj * sj;
+                const double fij = (si * si * eij + si * sj * eji) / den, fji = (si * si * eji + si * sj * eij) / den;
+                hdpq = fma(fij, dot(ab[0] + i * rT, ab[1] + j * rT), hdpq);
+                hdpq = fma(fji, dot(ab[0] + j * rT, ab[1] + i * rT), hdpq);
+            }
+            // left null space: (I - U_M U_M^T) dM V_K against P Q^T V_K
+            const int r = e / K, t = e % K;   // K3 x K entries
+            double v = A1[r * K + t];
+            if (r < N)
+                for (int b = 0; b < N; ++b) v = fma(-Um[b * N + r], EL[b * K + t], v);
+            hdpq = fma(v, dot(pr[0] + r * rT, ab[1] + t * rT), hdpq);
+        }
+        acc = block_sum(acc, red);
+        h2 = block_sum(h2, red);
+        hpq = block_sum(hpq, red);
+        hdh = block_sum(hdh, red);
+        hdpq = block_sum(hdpq, red);
+        rs = block_sum(rs, red);
+        // new factors: U' = [U* Q] U_M[:, :K] = U_f (R_U^{-1} X1) + [W1 dW1] (R_G^{-1} X2)
+        for (int e = tid; e < 2 * K3 * K; e += TR_THREADS) {
+            const int side = e / (K3 * K), x = e % (K3 * K), i = x / K, t = x % K;
+            const double* X = (side ? Vm : Um) + t * N;
+            double v = 0.0;
+            if (i < K) {
+                for (int l = 0; l < K; ++l) v = fma(ra[side][i * K + l], X[l], v);
+            } else {
+                for (int l = 0; l < K; ++l) v = fma(Ri[side][(i - K) * K2 + l], X[K + l], v);
+            }
+            a.S[side][x] = v;
+        }
+        if (tid < K) a.sigma_out[tid] = sg[tid];
+        if (tid == 0) {
+            RelaxResult r;
+            r.loss = (h2 - 2.0 * hpq + acc) / acc;
+            r.dloss_dzeta = 2.0 * (hdh - hdpq) / acc;
+            r.err = sqrt(rs / a.normD2);
+            r.sigma1 = sg[0];
+            r.sigma_r1 = sg[K];
+            r.sweeps = sweeps_s;
+            r.pad = 0;
+            *a.result = r;
+        }
     }
-}
 
-template <typename T>
-hipError_t relax_dispatch(const RelaxArgs& a, hipStream_t s) {
+    static __device__ void run(const Args& a) {
+        if (a.stage == 1) stage1(a);
+        else stage2(a);
+    }
+};
+
+template <typename T, int K> hipError_t relax_run(const RelaxArgs& a, hipStream_t s) {
     TrainPass<T> tp;
     memset(&tp, 0, sizeof(tp));
     tp.D = a.D;
@@ -447,33 +306,72 @@ hipError_t relax_dispatch(const RelaxArgs& a, hipStream_t s) {
     tp.n_rt = a.n_rt;
     tp.zeta = a.zeta;
     tp.itau = fmin(1.0 / a.tau, DBL_MAX);
-    tp.Lr = {cptr<T>(a.AL), a.K};
-    tp.Lc = {cptr<T>(a.BL), a.K};
-    tp.r0 = {cptr<T>(a.Uf), a.K};
-    tp.c0 = {cptr<T>(a.Vf), a.K};
+    tp.Lr = {cptr<T>(a.AL), K};
+    tp.Lc = {cptr<T>(a.BL), K};
+    tp.r0 = {cptr<T>(a.Uf), K};
+    tp.c0 = {cptr<T>(a.Vf), K};
     tp.Rp = a.R1;
     tp.Cp = a.R2;
     tp.scal = a.Rres;
-    const unsigned gs = (unsigned)(a.n_ct * a.n_rt);
-    const unsigned gsum = (unsigned)((((int64_t)a.m + a.n) * 2 * a.K + 255) / 256);
-    const unsigned gpan = (unsigned)(a.gU + a.gV);
+    hipLaunchKernelGGL((k_train_pass<T, T, K, TRAIN_STEP>), dim3((unsigned)(a.n_ct * a.n_rt)), dim3(TP_THREADS), 0, s,
+                       tp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    constexpr int K2 = 2 * K;
+    const int rt = a.rt_true;
+    const bool f32 = sizeof(T) == 4;
+    const PanelRef F[2] = {panel_ref(a.Uf, K, K, f32), panel_ref(a.Vf, K, K, f32)};
+    const PanelRef Y[2] = {panel_ref(a.RY1, K2, K2), panel_ref(a.RY2, K2, K2)};
+    const PanelRef PT[2] = {panel_ref(a.P, rt, rt), panel_ref(a.Q, rt, rt)};
+    const int rows[2] = {a.m, a.n}, tiles[2] = {a.n_ct, a.n_rt};
+    const double* part[2] = {a.R1, a.R2};
+    double* ry[2] = {a.RY1, a.RY2};
+    double* out[2] = {a.Uout, a.Vout};
+    StepArgs<RelaxTailArgs> base;
+    memset(&base, 0, sizeof(base));
+    base.gpart = a.gpartR;
+    base.cnt = &a.ctrl->cnt[CNT_RELAX];
+    RelaxTailArgs& t = base.tail;
+    t.rt = rt;
+    t.Rinv[0] = a.RUinv;
+    t.Rinv[1] = a.RVinv;
+    t.C = a.coef + 4 * 3 * K * K;   // after the two coefficient blocks (3K x 2K each)
+    t.scal = a.Rres;
+    t.tiles = a.n_tiles;
+    t.normD2 = a.normD2;
+    t.sigma_out = a.sigma_out;
+    t.result = a.result;
+    for (int side = 0; side < 2; ++side) {
+        t.G1[side] = a.gram + side * RX_WMAX * RX_WMAX;
+        t.G2[side] = a.gram2 + side * RX_WMAX * RX_WMAX;
+        t.S[side] = a.coef + side * 2 * 3 * K * K;
+        step_rows(&base.side[side], rows[side]);
+    }
+    StepArgs<RelaxTailArgs> s1 = base, s2 = base, s3 = base;
+    s1.tail.stage = 1;
+    s2.tail.stage = 2;
+    for (int side = 0; side < 2; ++side) {
+        double* g1 = a.gram + side * RX_WMAX * RX_WMAX;
+        double* g2 = a.gram2 + side * RX_WMAX * RX_WMAX;
+        step_sum(&s1.side[side], part[side], tiles[side], K2, ry[side]);
+        step_gram(&s1.side[side], {F[side], PT[side]}, {Y[side], PT[side]}, g1);
+        step_comb(&s2.side[side], {Y[side], F[side]}, t.S[side], K2, ry[side], K2);
+        step_gram(&s2.side[side], {Y[side]}, {Y[side], PT[side]}, g2);
+        step_comb(&s3.side[side], {F[side], Y[side]}, t.S[side], K, out[side], K);
+    }
+    if ((e = launch_step<RelaxTail<K>>(s1, s)) != hipSuccess) return e;
+    if ((e = launch_step<RelaxTail<K>>(s2, s)) != hipSuccess) return e;
+    return launch_step<RelaxTail<K>>(s3, s);
+}
+
+template <typename T> hipError_t relax_dispatch(const RelaxArgs& a, hipStream_t s) {
     switch (a.K) {
-#define RPCA_CASE(KK)                                                                            \
-    case KK:                                                                                     \
-        hipLaunchKernelGGL((k_train_pass<T, T, KK, TRAIN_STEP>), dim3(gs), dim3(TP_THREADS), 0, s, tp); \
-        hipLaunchKernelGGL((k_relax_sum<KK>), dim3(gsum), dim3(256), 0, s, a);                   \
-        hipLaunchKernelGGL((k_relax_gram<T, KK, true>), dim3(gpan), dim3(256), 0, s, a, (int)CNT_RELAX, a.gram);  \
-        hipLaunchKernelGGL((k_relax_complement<T, KK>), dim3(gpan), dim3(256), 0, s, a);          \
-        hipLaunchKernelGGL((k_relax_gram<T, KK, false>), dim3(gpan), dim3(256), 0, s, a, (int)CNT_RELAX, a.gram2); \
-        hipLaunchKernelGGL((k_relax_tail<KK>), dim3(1), dim3(WAVE), 0, s, a);                    \
-        hipLaunchKernelGGL((k_relax_update<T, KK>), dim3(gpan), dim3(256), 0, s, a);             \
-        break;
+#define RPCA_CASE(KK) case KK: return relax_run<T, KK>(a, s);
         RPCA_CASE(1) RPCA_CASE(2) RPCA_CASE(3) RPCA_CASE(4) RPCA_CASE(5) RPCA_CASE(6)
         RPCA_CASE(7) RPCA_CASE(8) RPCA_CASE(9) RPCA_CASE(10)
 #undef RPCA_CASE
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace

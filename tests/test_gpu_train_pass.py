@@ -1,7 +1,8 @@
 """The training passes over D (forward step, recomputation, reverse step) at
 the edges of their tiles (16-row blocks, 32 columns per wave, 256 per
-workgroup, 64-row tiles), at ranks around the widths of their products and
-with padded rows of D, against the FP64 oracle: losses of the forward steps
+workgroup, 64-row tiles) and the panel steps between them (64 rows per
+workgroup, several times that past 4096 rows), at ranks around the widths of
+their products and with padded rows of D, against the FP64 oracle: losses of the forward steps
 and every gradient of two unrolled bodies. Tolerances as for the ordinary
 sizes: the same FP64 algebra in another order (1e-8); FP32 data and factor
 copies (2e-4)."""
@@ -15,7 +16,7 @@ from paper_1711_05519_amd import rpca as R
 
 pytestmark = pytest.mark.gpu
 
-CASES = [(16, 32, 1), (17, 33, 4), (63, 255, 8), (65, 257, 9), (130, 511, 10), (2064, 30, 3)]
+CASES = [(16, 32, 1), (17, 33, 4), (63, 255, 8), (65, 257, 9), (130, 511, 10), (2064, 30, 3), (4200, 40, 2)]
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
