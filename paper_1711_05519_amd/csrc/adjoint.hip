@@ -79,7 +79,8 @@ template <int K> struct AdjTail {
     // SVD of M = [[C, R2^T], [R1, 0]], C = in[2] -> out[4] = U_M, out[5] = S, out[6] = V_M
     static __device__ __forceinline__ void chol(const Args& a, bool m) {
         __shared__ double G0[K * K], G1[K * K], R0[K * K], R1[K * K], I0[K * K], I1[K * K];
-        __shared__ double Mm[N * N], Vw[N * N], Uo[N * N], Vo[N * N], sg[N];
+        __shared__ double Mm[N * N], Uo[N * N], Vo[N * N], sg[N];
+        __shared__ JacobiLds<N> jac;
         const int tid = threadIdx.x;
         for (int e = tid; e < K * K; e += TR_THREADS) {
             G0[e] = a.in[0][e];
@@ -105,8 +106,7 @@ template <int K> struct AdjTail {
             Mm[e] = v;
         }
         __syncthreads();
-        if (tid < WAVE) wave_jacobi_svd<N, false>(Mm, Vw, sg, Uo, Vo);
-        __syncthreads();
+        jacobi_svd<N, false>(tid / WAVE, Mm, sg, Uo, Vo, &jac);
         for (int e = tid; e < N * N; e += TR_THREADS) {
             a.out[4][e] = Uo[e];
             a.out[6][e] = Vo[e];

@@ -174,7 +174,8 @@ __device__ __forceinline__ double w_mlp(const float* __restrict__ th, const doub
 
 // ---- the 2K x 2K step shared by the FP32 gather and the FP64 complement ------
 //
-// Single wave. Given C*, C2, the Grams G1 = W1^T W1 and G2 = W2^T W2 and
+// Single wave (a second one, in jacobi_right, takes the right singular vectors).
+// Given C*, C2, the Grams G1 = W1^T W1 and G2 = W2^T W2 and
 // R_U^{-1}, R_V^{-1}: R1, R2 by Cholesky, M = [[C*, R2^T], [R1, 0]], its SVD,
 // then either the next threshold (Algorithm 1) or the convergence test of the
 // initial subspace iteration, and the coefficients of the new factors
@@ -183,10 +184,10 @@ __device__ __forceinline__ double w_mlp(const float* __restrict__ th, const doub
 template <int K>
 __device__ __forceinline__ void w_svd_tail(const PanelArgs& a, Ctrl* ctrl, const double* cs, const double* c2,
                            const double* g1, const double* g2, const double* ru, const double* rv,
-                           bool gram_form, const float* th, bool th_lds) {
+                           bool gram_form, const float* th, bool th_lds, JacobiLds<2 * K>* jac, double* Vm) {
     constexpr int N = 2 * K;
     __shared__ double r1[K * K], r1i[K * K], r2[K * K], r2i[K * K];
-    __shared__ double Ma[N * N], Mv[N * N], Um[N * N], Vm[N * N], sg[N];
+    __shared__ double Ma[N * N], Um[N * N], sg[N];
     __shared__ double x1[K * K], x2[K * K], z1[K * K], z2[K * K], t1[K * K], t2[K * K];
     const int lane = lane_id();
     w_chol_inv2<K>(g1, r1, r1i, g2, r2, r2i);
@@ -203,7 +204,7 @@ __device__ __forceinline__ void w_svd_tail(const PanelArgs& a, Ctrl* ctrl, const
     // sigma_1)^2 are not rotated against each other: both end below the
     // dropping level below, and such a rotation moves no other column.
     const double neg2 = ctrl->sigma_dead * ctrl->sigma_dead / N;
-    const int sweeps = wave_jacobi_svd<N>(Ma, Mv, sg, Um, Vm, neg2, ctrl->single ? JACOBI_QUAD_F32 : JACOBI_QUAD);
+    const int sweeps = jacobi_left<N, true>(Ma, sg, Um, jac, neg2, ctrl->single ? JACOBI_QUAD_F32 : JACOBI_QUAD);
     // Triplets whose singular value is at the rounding level of the products
     // (sigma_j <= sigma_dead * sigma_1) carry no information about the range
     // of P_T(Z): their vectors are noise and need not be orthogonal to U*, so
@@ -571,7 +572,13 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
         }
     }
     block_resid<NT>(a.resid, a.n_tiles, sigma_stage, rv_, rw_, part, rsum);
-    if (threadIdx.x >= WAVE) return;
+    if (threadIdx.x >= 2 * WAVE) return;
+    __shared__ JacobiLds<2 * K> jac;
+    __shared__ double Vm[4 * K * K];
+    if (threadIdx.x >= WAVE) {
+        if (GRAM) jacobi_right<2 * K>(Vm, &jac);
+        return;
+    }
     const int lane = lane_id();
     if (lane < CW) reinterpret_cast<uint32_t*>(&cl)[lane] = cword;
     Ctrl* const cg = ctrl;   // the control block in device memory
@@ -630,7 +637,9 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
         w_mm2<K, true>(cs, cs, craw, c2, c2, craw2);
         for (int e = lane; e < K * K; e += WAVE) { g1[e] -= craw[e]; g2[e] -= craw2[e]; }
         wave_sync();
-        w_svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, true, a.mlp ? th_s : nullptr, true);
+        w_svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, true, a.mlp ? th_s : nullptr, true, &jac, Vm);
+    } else if (GRAM) {
+        jacobi_none<2 * K>(&jac);
     }
     wave_sync();
     if (lane < CW) reinterpret_cast<uint32_t*>(cg)[lane] = reinterpret_cast<const uint32_t*>(&cl)[lane];
@@ -683,9 +692,15 @@ __global__ __launch_bounds__(PANEL_THREADS) void k_complement(PanelArgs a_) {
     double* g1 = gg;
     double* g2 = gg + K * K;
     block_sum_partials<K * K, 2, PANEL_THREADS>(a.gpart, a.gU, a.gV, gg, part);
-    if (threadIdx.x >= WAVE) return;
+    if (threadIdx.x >= 2 * WAVE) return;
+    __shared__ JacobiLds<2 * K> jac;
+    __shared__ double Vm[4 * K * K];
+    if (threadIdx.x >= WAVE) {
+        jacobi_right<2 * K>(Vm, &jac);
+        return;
+    }
     if (lane_id() == 0) ctrl->cnt[CNT_COMPLEMENT] = 0;
-    w_svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, false, a.mlp, false);
+    w_svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, false, a.mlp, false, &jac, Vm);
 }
 
 // ---- kernel 3: new factors (or entry from a given state), Trim, new bases ----

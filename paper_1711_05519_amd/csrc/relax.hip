@@ -120,7 +120,8 @@ template <int K> struct RelaxTail {
         constexpr int N = K2;
         __shared__ double RG[2][K2 * K2], Ri[2][K2 * K2], GG[2][K2 * K2];
         __shared__ double ra[2][K * K];
-        __shared__ double Mv[N * N], Um[N * N], Vm[N * N], sg[N];
+        __shared__ double Um[N * N], Vm[N * N], sg[N];
+        __shared__ JacobiLds<N> jac;
         __shared__ double dM[K3 * K3], A1[K3 * K], EL[N * K], A2[K * K3], ET[K * K3];
         __shared__ double pr[2][K3 * RX_TRUE_MAX], ab[2][K3 * RX_TRUE_MAX];
         __shared__ double red[TR_WAVES];
@@ -167,8 +168,8 @@ template <int K> struct RelaxTail {
             pr[side][i * rT + q] = v;
         }
         __syncthreads();
+        const int sweeps = jacobi_svd<N, false>(tid / WAVE, M, sg, Um, Vm, &jac);   // Um, Vm column-major
         if (tid < WAVE) {
-            const int sweeps = wave_jacobi_svd<N, false>(M, Mv, sg, Um, Vm);   // Um, Vm column-major
             const double cut = 1e-12 * sg[0];
             for (int e = tid; e < N * N; e += WAVE)
                 if (sg[e / N] <= cut) Um[e] = 0.0;

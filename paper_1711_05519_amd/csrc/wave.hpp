@@ -295,121 +295,284 @@ template <int LP> __device__ inline double group_sum(double x) {
 
 constexpr int pow2_floor(int x) { int p = 1; while (p * 2 <= x) p *= 2; return p; }
 
-// One-sided (Hestenes) Jacobi SVD of the N x N matrix A (LDS, column-major),
-// run by a single wave: the N/2 disjoint column pairs of a round-robin round
-// are processed at once, LP lanes per pair, with DPP reductions for the three
-// inner products. A pair is rotated when |a_p . a_q| > JACOBI_EPS ||a_p|| ||a_q||
-// and above the absolute floor JACOBI_ABS ||A||_F^2 (pairs of negligible
-// columns would otherwise rotate on rounding noise), unless both columns have
-// ||a||^2 <= neg2 ||A||_F^2 (columns the caller discards: a rotation never
-// raises the smaller norm of a pair). Sweeps stop when no pair was rotated, or
-// (QUAD_STOP) after a sweep whose rotation angles were all below
-// quad (default JACOBI_QUAD); callers that difference the result keep the
-// confirming sweep. On return
-// sig[] is descending and Uo/Vo hold the left/right singular vectors as
-// columns (column-major). Returns the sweep count.
-template <int N, bool QUAD_STOP = true>
-__device__ __forceinline__ int wave_jacobi_svd(double* A, double* V, double* sig, double* Uo, double* Vo, double neg2 = 0.0,
-                                               double quad = JACOBI_QUAD) {
+// ---- one-sided (Hestenes) Jacobi SVD of a small matrix -------------------------
+//
+// A (N x N, LDS, column-major) in the registers of one wave: the N / 2 disjoint
+// column pairs of a round-robin round are processed at once. A pair is rotated
+// when |a_p . a_q| > JACOBI_EPS ||a_p|| ||a_q|| and above the absolute floor
+// JACOBI_ABS ||A||_F^2 (pairs of negligible columns would otherwise rotate on
+// rounding noise), unless both columns have ||a||^2 <= neg2 ||A||_F^2 (columns the
+// caller discards: a rotation never raises the smaller norm of a pair). Sweeps
+// stop when no pair was rotated, or (QUAD_STOP) after a sweep whose rotation
+// angles were all below quad (default JACOBI_QUAD); callers that difference
+// the result keep the confirming sweep.
+//
+// Bound by one wave's instruction stream: a round is a serial chain (an inner
+// product, a rotation, the columns handed to the next round's pairs) and a
+// sweep N - 1 of them. So everything off that chain is kept off it:
+//   - Lane l holds rows l / PL + NSUB u of the pair l % PL: handing the columns
+//     on is a move by one lane (DPP), inner products are sums over the upper
+//     lane bits (DPP, v_permlane swaps), and LDS is only written.
+//   - The right vectors, which no round reads, are rotated by a second wave from
+//     the cosines and sines left in LDS, one sweep behind (two buffers, one
+//     barrier per sweep).
+//   - Squared norms travel with their columns and are formed anew each sweep: a
+//     rotation changes them by +- tan(theta) (a_p . a_q). What that loses to
+//     cancellation is below the rounding of the largest column's square, where
+//     pairs are under the absolute floor.
+//   - The angle is found in FP32 (A is scaled by a power of two to a norm near
+//     1), tan(theta) good to about 2^-22; cosine and sine of that angle are formed
+//     from it in FP64, so the rotation is orthogonal to FP64 and only the
+//     coupling it leaves is that fraction of the one it found. A sweep already
+//     leaves the square of its angles, so what a sweep that ends the iteration
+//     leaves is 2^-22 of an angle below quad: rounding.
+// With the columns in LDS, both matrices in one wave and FP64 angles a round took
+// 0.36 us at N = 12 and 0.55 at N = 22; now 0.24 and 0.33 (gather of the
+// initialisation at m = n = 10^4, 2K = 12: 39 -> 30 us; at 2 10^4, 2K = 22: 115 ->
+// 90 us; FP64 complement at n = 1000, 2K = 12: 32 -> 24 us).
+//
+// jacobi_svd is called by every live wave of the workgroup with its index: wave 0
+// works on A, wave 1 on the right vectors, others only take part in the
+// barriers. On return (after a barrier) sig[] is descending and Uo / Vo hold
+// the left / right singular vectors as columns (column-major). Wave 0 returns the
+// sweep count. A is unchanged.
+template <int N> struct JacobiGeom {
     static_assert(N % 2 == 0 && N <= 2 * KMAX, "even N up to 2*KMAX");
-    constexpr int NP = N / 2;
-    constexpr int LP0 = pow2_floor(WAVE / NP);
-    constexpr int LP = LP0 > 16 ? 16 : LP0;
-    constexpr int E = (N + LP - 1) / LP;
-    const int lane = lane_id();
-    double fro = 0.0;
-    for (int e = lane; e < N * N; e += WAVE) {
-        V[e] = ((e / N) == (e % N)) ? 1.0 : 0.0;
-        fro = fma(A[e], A[e], fro);
+    static constexpr int P = N / 2;                 // pairs
+    static constexpr int PL = P <= 8 ? 8 : 16;      // lanes per group of pairs
+    static constexpr int NSUB = WAVE / PL;          // lanes per pair
+    static constexpr int E = (N + NSUB - 1) / NSUB; // rows of a column per lane
+};
+enum JacobiFlag : int { JACOBI_GO = 0, JACOBI_LAST = 1, JACOBI_NONE = 2 };
+template <int N> struct JacobiLds {
+    double cs[2][N - 1][JacobiGeom<N>::PL][2];      // the rotations of a sweep, two sweeps deep
+    double norm[N];
+    int rank[N];
+    int flag[2];
+};
+
+__device__ __forceinline__ double jacobi_swap_sum(double x, bool by32) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    const auto l = by32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                        : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = by32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                        : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __longlong_as_double((int64_t)(((uint64_t)h[0] << 32) | l[0])) +
+           __longlong_as_double((int64_t)(((uint64_t)h[1] << 32) | l[1]));
+}
+// sum over the lanes of a pair (the lane bits above log2 PL), in every lane
+template <int PL> __device__ __forceinline__ double jacobi_sum(double x) {
+    if constexpr (PL == 8) x += dpp64<0x128>(x);   // row_ror:8: lane ^ 8
+    x = jacobi_swap_sum(x, false);                 // lane ^ 16
+    return jacobi_swap_sum(x, true);               // lane ^ 32
+}
+
+// Hands the columns on: position 0's t stays, the others move one position down
+// in t, round its end into b and up in b.
+template <int N> __device__ __forceinline__ void jacobi_hand_on(double& t, double& b, bool first, bool last) {
+    if constexpr (N > 2) {
+        const double dn = dpp64<0x101>(t), up = dpp64<0x111>(b);   // row_shl:1 (from lane + 1), row_shr:1
+        t = first ? t : (last ? b : dn);
+        b = first ? dn : up;
     }
+}
+
+// Rotates the pair (t, b) and hands it on.
+template <int N>
+__device__ __forceinline__ void jacobi_turn(double (&t)[JacobiGeom<N>::E], double (&b)[JacobiGeom<N>::E], double c,
+                                            double s, bool first, bool last) {
+    using G = JacobiGeom<N>;
+#pragma unroll
+    for (int u = 0; u < G::E; ++u) {
+        double x = fma(c, t[u], -(s * b[u])), y = fma(s, t[u], c * b[u]);
+        jacobi_hand_on<N>(x, y, first, last);
+        t[u] = x;
+        b[u] = y;
+    }
+}
+
+template <int N, bool QUAD_STOP>
+__device__ __forceinline__ int jacobi_left(const double* A, double* sig, double* Uo, JacobiLds<N>* J, double neg2,
+                                           double quad) {
+    using G = JacobiGeom<N>;
+    const int lane = lane_id(), p = lane & (G::PL - 1), g = lane / G::PL;
+    const bool first = p == 0, last = p == G::P - 1, in = p < G::P;
+    double t[G::E], b[G::E];
+#pragma unroll
+    for (int u = 0; u < G::E; ++u) {
+        const int e = g + G::NSUB * u;
+        const bool ok = in && e < N;
+        t[u] = ok ? A[p * N + e] : 0.0;
+        b[u] = ok ? A[(N - 1 - p) * N + e] : 0.0;
+    }
+    double fro = 0.0;
+#pragma unroll
+    for (int u = 0; u < G::E; ++u) fro = fma(t[u], t[u], fma(b[u], b[u], fro));
     for (int off = 32; off > 0; off >>= 1) fro += __shfl_xor(fro, off, WAVE);
+    // 2^-sh A has a squared norm in [1/4, 1] (sh = 0 for a zero or non-finite one)
+    const int sh = (fro > 0.0 && fro < 1.7976931348623157e308) ? (ilogb(fro) + 2) >> 1 : 0;
+#pragma unroll
+    for (int u = 0; u < G::E; ++u) {
+        t[u] = ldexp(t[u], -sh);
+        b[u] = ldexp(b[u], -sh);
+    }
+    fro = ldexp(fro, -2 * sh);
     const double floor_abs = JACOBI_ABS * fro;
     const double floor_neg = neg2 * fro;
-    wave_sync();
-    const int q = lane / LP, g = lane % LP;
-    int sweep = 0;
-    for (; sweep < JACOBI_MAX_SWEEPS; ++sweep) {
-        bool rotated = false, large = false;
-        for (int rd = 0; rd < N - 1; ++rd) {
-            if (q < NP) {
-                const int a = (q == 0) ? 0 : ((q - 1 + rd) % (N - 1)) + 1;
-                const int b = ((N - 2 - q + rd) % (N - 1)) + 1;
-                double xa[E], xb[E], va[E], vb[E];
-                double al = 0.0, be = 0.0, ga = 0.0;
+    const float quad_t = (float)quad;   // below it the tangent of an angle is its sine
+    int sweep = 0, extra = 0;
+    for (;; ++sweep) {
+        float tmax = 0.f;
+        double al = 0.0, be = 0.0;
 #pragma unroll
-                for (int u = 0; u < E; ++u) {
-                    const int e = g + LP * u;
-                    const bool ok = e < N;
-                    xa[u] = ok ? A[a * N + e] : 0.0;
-                    xb[u] = ok ? A[b * N + e] : 0.0;
-                    va[u] = ok ? V[a * N + e] : 0.0;
-                    vb[u] = ok ? V[b * N + e] : 0.0;
-                    al = fma(xa[u], xa[u], al);
-                    be = fma(xb[u], xb[u], be);
-                    ga = fma(xa[u], xb[u], ga);
-                }
-                al = group_sum<LP>(al);
-                be = group_sum<LP>(be);
-                ga = group_sum<LP>(ga);
-                if (ga * ga > (JACOBI_EPS * JACOBI_EPS) * (al * be) && fabs(ga) > floor_abs &&
-                    fmax(al, be) > floor_neg) {
-
-                    // rotation by theta, |theta| <= pi/4, tan 2 theta = 2 ga / (be - al):
-                    // with h = sqrt((be - al)^2 + 4 ga^2), cos 2 theta = |be - al| / h,
-                    // c = sqrt((1 + cos 2 theta) / 2), s = sign(be - al) ga / (h c);
-                    // two reciprocal square roots, no division
-                    const double dl = be - al;
-                    const double rh = rsqrt(fma(dl, dl, 4.0 * ga * ga));
-                    const double c2 = fma(0.5 * fabs(dl), rh, 0.5);
-                    const double ic = rsqrt(c2);
-                    const double c = c2 * ic;
-                    const double s = (dl >= 0.0 ? ga : -ga) * rh * ic;
-                    large = large || fabs(s) > quad;
-#pragma unroll
-                    for (int u = 0; u < E; ++u) {
-                        const int e = g + LP * u;
-                        if (e < N) {
-                            A[a * N + e] = c * xa[u] - s * xb[u];
-                            A[b * N + e] = s * xa[u] + c * xb[u];
-                            V[a * N + e] = c * va[u] - s * vb[u];
-                            V[b * N + e] = s * va[u] + c * vb[u];
-                        }
-                    }
-                    rotated = true;
-                }
-            }
-            wave_sync();
+        for (int u = 0; u < G::E; ++u) {
+            al = fma(t[u], t[u], al);
+            be = fma(b[u], b[u], be);
         }
-        if (!__any(rotated)) break;
-        if (QUAD_STOP && !__any(large)) { ++sweep; break; }
+        al = jacobi_sum<G::PL>(al);
+        be = jacobi_sum<G::PL>(be);
+        double* cs = &J->cs[sweep & 1][0][p][0];
+        for (int rd = 0; rd < N - 1; ++rd, cs += 2 * G::PL) {
+            double ga = 0.0;
+#pragma unroll
+            for (int u = 0; u < G::E; ++u) ga = fma(t[u], b[u], ga);
+            ga = jacobi_sum<G::PL>(ga);
+            // rotation by theta, |theta| <= pi/4: tan 2 theta = 2 ga / (be - al),
+            // tan theta = sign(be - al) 2 ga / (|be - al| + sqrt((be - al)^2 + 4 ga^2))
+            const float dl = (float)(be - al), g2 = (float)(ga + ga);
+            const float hyp = __builtin_amdgcn_sqrtf(fmaf(dl, dl, g2 * g2));
+            const float tn = copysignf(1.f, dl) * g2 * __builtin_amdgcn_rcpf(fabsf(dl) + hyp);
+            // (lanes past the last pair hold what was handed past it: no pair)
+            const bool rot = in & (ga * ga > (JACOBI_EPS * JACOBI_EPS) * (al * be)) & (fabs(ga) > floor_abs) &
+                             ((al > floor_neg) | (be > floor_neg));
+            const float tf = rot ? tn : 0.f;
+            tmax = fmaxf(tmax, fabsf(tf));
+            // c = 1 / sqrt(1 + tan^2) by one third-order step from the FP32 value, s = tan c
+            const double tt = (double)tf, q = fma(tt, tt, 1.0);
+            const double y = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.f));
+            const double e = fma(-q * y, y, 1.0);
+            const double c = fma(y * e, fma(0.375, e, 0.5), y), s = tt * c;
+            cs[0] = c;
+            cs[1] = s;
+            al = fma(-tt, ga, al);
+            be = fma(tt, ga, be);
+            jacobi_turn<N>(t, b, c, s, first, last);
+            jacobi_hand_on<N>(al, be, first, last);
+        }
+        bool stop = !__any(tmax > 0.f);
+        if (!stop && QUAD_STOP && !__any(tmax > quad_t)) {
+            stop = true;
+            extra = 1;
+        }
+        if (!stop && sweep == JACOBI_MAX_SWEEPS - 1) {
+            stop = true;
+            extra = 1;
+        }
+        if (lane == 0) J->flag[sweep & 1] = stop ? JACOBI_LAST : JACOBI_GO;
+        __syncthreads();
+        if (stop) break;
     }
-    // column norms, ranks (descending, ties by index), normalised outputs
-    if (lane < N) {
-        double acc = 0.0;
-        for (int e = 0; e < N; ++e) acc = fma(A[lane * N + e], A[lane * N + e], acc);
-        sig[lane] = sqrt(acc);
+    // column norms, ranks (descending, ties by index), normalised outputs; the
+    // columns are where they started
+    double nt = 0.0, nb = 0.0;
+#pragma unroll
+    for (int u = 0; u < G::E; ++u) {
+        nt = fma(t[u], t[u], nt);
+        nb = fma(b[u], b[u], nb);
+    }
+    nt = sqrt(jacobi_sum<G::PL>(nt));
+    nb = sqrt(jacobi_sum<G::PL>(nb));
+    if (in && g == 0) {
+        J->norm[p] = nt;
+        J->norm[N - 1 - p] = nb;
     }
     wave_sync();
-    double sj = 0.0;
-    int rank = 0;
     if (lane < N) {
-        sj = sig[lane];
+        const double sj = J->norm[lane];
+        int rank = 0;
+#pragma unroll
         for (int i = 0; i < N; ++i) {
-            const double si = sig[i];
+            const double si = J->norm[i];
             rank += (si > sj) || (si == sj && i < lane);
         }
+        J->rank[lane] = rank;
+        sig[rank] = ldexp(sj, sh);
     }
-    wave_sync();
-    if (lane < N) {
-        sig[rank] = sj;
-        const double inv = sj > 0.0 ? 1.0 / sj : 0.0;
-        for (int e = 0; e < N; ++e) {
-            Uo[rank * N + e] = A[lane * N + e] * inv;
-            Vo[rank * N + e] = V[lane * N + e];
+    __syncthreads();
+    if (in) {
+        const int rt = J->rank[p], rb = J->rank[N - 1 - p];
+        const double it = nt > 0.0 ? 1.0 / nt : 0.0, ib = nb > 0.0 ? 1.0 / nb : 0.0;
+#pragma unroll
+        for (int u = 0; u < G::E; ++u) {
+            const int e = g + G::NSUB * u;
+            if (e < N) {
+                Uo[rt * N + e] = t[u] * it;
+                Uo[rb * N + e] = b[u] * ib;
+            }
         }
     }
-    wave_sync();
-    return sweep + 1;
+    __syncthreads();
+    return sweep + 1 + extra;
+}
+
+template <int N> __device__ __forceinline__ void jacobi_right(double* Vo, JacobiLds<N>* J) {
+    using G = JacobiGeom<N>;
+    const int lane = lane_id(), p = lane & (G::PL - 1), g = lane / G::PL;
+    const bool first = p == 0, last = p == G::P - 1, in = p < G::P;
+    double t[G::E], b[G::E];
+#pragma unroll
+    for (int u = 0; u < G::E; ++u) {
+        const int e = g + G::NSUB * u;
+        t[u] = (in && e == p) ? 1.0 : 0.0;
+        b[u] = (in && e == N - 1 - p) ? 1.0 : 0.0;
+    }
+    const int pc = in ? p : 0;
+    for (int sweep = 0;; ++sweep) {
+        __syncthreads();
+        const int flag = J->flag[sweep & 1];
+        if (flag == JACOBI_NONE) return;
+#pragma unroll 2
+        for (int rd = 0; rd < N - 1; ++rd)
+            jacobi_turn<N>(t, b, J->cs[sweep & 1][rd][pc][0], J->cs[sweep & 1][rd][pc][1], first, last);
+        if (flag == JACOBI_LAST) break;
+    }
+    __syncthreads();
+    if (in) {
+        const int rt = J->rank[p], rb = J->rank[N - 1 - p];
+#pragma unroll
+        for (int u = 0; u < G::E; ++u) {
+            const int e = g + G::NSUB * u;
+            if (e < N) {
+                Vo[rt * N + e] = t[u];
+                Vo[rb * N + e] = b[u];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Wave 0 of a workgroup whose wave 1 waits in jacobi_right: no SVD this time.
+template <int N> __device__ __forceinline__ void jacobi_none(JacobiLds<N>* J) {
+    if (lane_id() == 0) J->flag[0] = JACOBI_NONE;
+    __syncthreads();
+}
+
+template <int N, bool QUAD_STOP = true>
+__device__ __forceinline__ int jacobi_svd(int wave, const double* A, double* sig, double* Uo, double* Vo,
+                                          JacobiLds<N>* J, double neg2 = 0.0, double quad = JACOBI_QUAD) {
+    if (wave == 0) return jacobi_left<N, QUAD_STOP>(A, sig, Uo, J, neg2, quad);
+    if (wave == 1) {
+        jacobi_right<N>(Vo, J);
+        return 0;
+    }
+    for (int sweep = 0;; ++sweep) {
+        __syncthreads();
+        if (J->flag[sweep & 1] != JACOBI_GO) break;
+    }
+    __syncthreads();
+    __syncthreads();
+    return 0;
 }
 
 // ---- the update kernel's closing sums -----------------------------------------
