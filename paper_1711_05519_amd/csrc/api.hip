@@ -321,15 +321,30 @@ struct Layout {
 // workspace is sized for the largest tiling any device can ask for.
 constexpr int STREAM_MAX_SLOTS = 2048;   // 256 CUs x 8 workgroups of 256 threads
 constexpr int STREAM_MIN_TM = 64;
+// Problems whose 64-row tiles would not give every CU a workgroup use tiles of
+// down to 16 rows (4 per wave) until they do. (Solves: FP64 300 x 200 r = 3, 5 -> 19
+// tiles, 12 -> 8 us a pass, 1135 -> 1021 us; FP64 1000 x 1000 r = 5, 64 -> 252 tiles, 16 -> 10 us,
+// 1543 -> 1442 us.) FP64 only: an FP32 solve stays on the tiles a batch of such
+// instances uses (finer ones would grow its memory), so that both sum in the
+// same order and keep the same entries above the thresholds.
+constexpr int STREAM_MIN_TM_SMALL = 16;
+constexpr int STREAM_SMALL_TILES = 256;
 
-int n_rt_for(int m, int n_ct, int slots) {
+int n_rt_for(int m, int n_ct, int slots, bool fine_tiles) {
     int n_rt = slots / n_ct;
     if (n_rt < 1) n_rt = 1;
-    const int cap = (m + STREAM_MIN_TM - 1) / STREAM_MIN_TM;
+    int cap = (m + STREAM_MIN_TM - 1) / STREAM_MIN_TM;
+    if (fine_tiles) {
+        int fine = (m + STREAM_MIN_TM_SMALL - 1) / STREAM_MIN_TM_SMALL;
+        if (fine > STREAM_SMALL_TILES / n_ct) fine = STREAM_SMALL_TILES / n_ct;
+        if (cap < fine) cap = fine;
+    }
     return n_rt < cap ? n_rt : cap;
 }
 
-Layout make_layout(const rpca_params* p) {
+// batched: the layout of one instance of a batch: 64-row tiles and more (the
+// instances fill the device), without the panels that no kernel of a batch uses.
+Layout make_layout(const rpca_params* p, bool batched = false) {
     Layout L;
     L.K_main = p->r;
     L.K_init = init_block_of(p);
@@ -338,7 +353,7 @@ Layout make_layout(const rpca_params* p) {
     L.acc = L.elt;
     const int m = (int)p->m, n = (int)p->n;
     L.n_ct = (n + STREAM_TN - 1) / STREAM_TN;
-    L.n_rt_max = n_rt_for(m, L.n_ct, STREAM_MAX_SLOTS);
+    L.n_rt_max = n_rt_for(m, L.n_ct, STREAM_MAX_SLOTS, !batched && p->dtype == RPCA_F64);
     L.gU = (m + PANEL_THREADS - 1) / PANEL_THREADS;
     L.gV = (n + PANEL_THREADS - 1) / PANEL_THREADS;
     const int rpb = gather_threads_for(m, n) / GATHER_SPLIT;
@@ -355,8 +370,10 @@ Layout make_layout(const rpca_params* p) {
     L.off_gpart = take(sizeof(double) * (size_t)(g_gather > L.gU + L.gV ? g_gather : L.gU + L.gV) * GPART_STRIDE);
     const size_t pm = sizeof(double) * (size_t)m * L.KW, pn = sizeof(double) * (size_t)n * L.KW;
     L.off_Y1 = take(pm); L.off_Y2 = take(pn);
-    L.off_W1 = take(pm); L.off_W2 = take(pn);
-    L.off_Ap = take(pm); L.off_Bp = take(pn);
+    // complements W (FP64 only) and the exact trimmed factors (rpca_trim only)
+    const bool has_w = !batched || p->dtype == RPCA_F64;
+    L.off_W1 = take(has_w ? pm : 0); L.off_W2 = take(has_w ? pn : 0);
+    L.off_Ap = take(batched ? 0 : pm); L.off_Bp = take(batched ? 0 : pn);
     L.off_Unew = take(pm); L.off_Vnew = take(pn);
     const size_t tm = L.elt * (size_t)m * L.KW, tn = L.elt * (size_t)n * L.KW;
     L.off_Uf = take(tm); L.off_Vf = take(tn);
@@ -415,12 +432,12 @@ struct Ctx {
     template <typename X> X* at(size_t off) const { return reinterpret_cast<X*>(ws + off); }
 };
 
-int make_ctx(const rpca_params* p, void* ws, size_t ws_bytes, void* stream, Ctx* c) {
+int make_ctx(const rpca_params* p, void* ws, size_t ws_bytes, void* stream, Ctx* c, bool batched = false) {
     RPCA_TRY(validate(p));
     DeviceInfo* dev = nullptr;
     RPCA_TRY(device_info(&dev));
     c->p = p;
-    c->L = make_layout(p);
+    c->L = make_layout(p, batched);
     if (!ws || ((uintptr_t)ws & 255u) != 0 || ws_bytes < c->L.total) return RPCA_EWORKSPACE;
     c->ws = static_cast<char*>(ws);
     c->s = static_cast<hipStream_t>(stream);
@@ -478,11 +495,11 @@ Geo geo_for(const Ctx& c, int K, bool rebuild, bool mx = false) {
         // that the last, partly filled round is a small part of the pass
         const int64_t per = (int64_t)c.L.n_ct * c.batch;
         const int want = (int)((2 * (int64_t)slots + per - 1) / per);
-        n_rt = n_rt_for(m, c.L.n_ct, want * c.L.n_ct);
-        if (n_rt > c.L.n_rt_max) n_rt = c.L.n_rt_max;
+        n_rt = n_rt_for(m, c.L.n_ct, want * c.L.n_ct, false);
     } else {
-        n_rt = n_rt_for(m, c.L.n_ct, slots < STREAM_MAX_SLOTS ? slots : STREAM_MAX_SLOTS);
+        n_rt = n_rt_for(m, c.L.n_ct, slots < STREAM_MAX_SLOTS ? slots : STREAM_MAX_SLOTS, c.dtype == RPCA_F64);
     }
+    if (n_rt > c.L.n_rt_max) n_rt = c.L.n_rt_max;
     int TM = (m + n_rt - 1) / n_rt;
     TM = (TM + STREAM_WAVES - 1) / STREAM_WAVES * STREAM_WAVES;
     Geo g;
@@ -509,8 +526,6 @@ StreamArgs stream_args(const Ctx& c, const void* D, int body, const Geo& g) {
     a.TM = g.TM;
     a.n_ct = c.L.n_ct;
     a.n_rt = g.n_rt;
-    const size_t row_bytes = (size_t)c.p->ldd * c.L.elt;
-    a.vec_ok = (((uintptr_t)D & 15u) == 0 && (row_bytes & 15u) == 0 && (c.slab & 15) == 0) ? 1 : 0;
     a.body = body;
     a.batch = c.batch;
     a.slab = c.slab;
@@ -1146,7 +1161,7 @@ int rpca_solve_many(int32_t count, const void* const* D, const rpca_params* cons
 int rpca_batch_layout_of(const rpca_params* p, rpca_batch_layout* out) {
     if (!out) return RPCA_EINVAL;
     RPCA_TRY(validate(p));
-    const Layout L = make_layout(p);
+    const Layout L = make_layout(p, true);
     const size_t elt = p->dtype == RPCA_F32 ? 4 : 8;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -1227,7 +1242,7 @@ int rpca_solve_batch(int32_t count, void* slabs, const rpca_params* params, rpca
     RPCA_TRY(rpca_batch_layout_of(p, &bl));
     char* base = static_cast<char*>(slabs);
     Ctx c;
-    RPCA_TRY(make_ctx(p, base + bl.off_ws, make_layout(p).total, stream, &c));
+    RPCA_TRY(make_ctx(p, base + bl.off_ws, make_layout(p, true).total, stream, &c, true));
     c.batch = count;
     c.slab = (int64_t)bl.slab_bytes;
     c.events = false;

@@ -223,18 +223,6 @@ __device__ inline int xcd_tile(int b, int G) {
 // size measured (m = n = 5000: solve 2.09 -> 2.43 ms). Passes over FP32 D use
 // them for blocks of up to D_LOADS_NT_KMAX columns.
 constexpr int D_LOADS_NT_KMAX = 6;
-typedef float nt_float4 __attribute__((ext_vector_type(4)));
-typedef double nt_double2 __attribute__((ext_vector_type(2)));
-template <bool NT> __device__ inline float4 load_d(const float4* p) {
-    if constexpr (!NT) return *p;
-    const nt_float4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_float4*>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-template <bool NT> __device__ inline double2 load_d(const double2* p) {
-    if constexpr (!NT) return *p;
-    const nt_double2 v = __builtin_nontemporal_load(reinterpret_cast<const nt_double2*>(p));
-    return make_double2(v.x, v.y);
-}
 template <bool NT> __device__ inline float load_d(const float* p) {
     if constexpr (!NT) return *p;
     return __builtin_nontemporal_load(p);
@@ -242,6 +230,37 @@ template <bool NT> __device__ inline float load_d(const float* p) {
 template <bool NT> __device__ inline double load_d(const double* p) {
     if constexpr (!NT) return *p;
     return __builtin_nontemporal_load(p);
+}
+
+// Element-aligned 16-byte vectors: the hardware takes 16-byte accesses at any
+// 4-byte address, so code using them needs no alignment of rows.
+template <typename T> struct Vec16u;
+template <> struct Vec16u<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Vec16u<double> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
+
+// Rows j .. j + R - 1 of an n x K panel into registers, zeros past the first
+// nv of them. The R K values are contiguous: whole vectors when all R are there.
+// (One conditional 4-byte load per value, which this replaces in the passes, held
+// each workgroup back by as many dependent branches: loop pass over 10^4 x 10^4
+// at K = 5 86 -> 75 us, over 25344 x 2000 at K = 2 69 -> 36 us, 5.7 TB/s.)
+template <typename T, int R, int K>
+__device__ __forceinline__ void load_panel_rows(const T* __restrict__ P, int j, int nv, T (&b)[R][K]) {
+    constexpr int VW = 16 / (int)sizeof(T);
+    static_assert((R * K) % VW == 0, "whole vectors");
+    const T* p = P + (size_t)j * K;
+    if (nv == R) {
+#pragma unroll
+        for (int v = 0; v < R * K / VW; ++v) {
+            const auto x = *reinterpret_cast<const typename Vec16u<T>::type*>(p + v * VW);
+#pragma unroll
+            for (int q = 0; q < VW; ++q) b[(v * VW + q) / K][(v * VW + q) % K] = x[q];
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < R; ++s)
+#pragma unroll
+            for (int t = 0; t < K; ++t) b[s][t] = s < nv ? p[s * K + t] : T(0);
+    }
 }
 
 // p moved by off bytes (the data of another instance of a batched launch);

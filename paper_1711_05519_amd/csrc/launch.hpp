@@ -23,7 +23,6 @@ struct StreamArgs {
     double* resid;        // [n_ct * n_rt] partial residual sums
     int32_t TM;           // rows per tile
     int32_t n_ct, n_rt;
-    int32_t vec_ok;       // 1 if D rows are 16-byte aligned (vector loads allowed)
     int32_t body;         // Body: gating of the launch
     int32_t batch;        // instances in the launch (grid y); every pointer above is
     int64_t slab;         // instance 0's, instance i's lies i * slab bytes further
@@ -37,7 +36,7 @@ struct StreamArgs {
 // separately so the compiler can treat them as non-aliasing).
 struct StreamGeom {
     int64_t ldd;
-    int32_t m, n, TM, n_ct, n_rt, vec_ok, body;
+    int32_t m, n, TM, n_ct, n_rt, body;
     int64_t slab;         // bytes between the instances of a batched launch (0: one instance)
     double* post_gpart;   // see StreamArgs (null: the pass never completes an update)
     Small* post_small;

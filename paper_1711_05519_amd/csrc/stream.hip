@@ -141,65 +141,38 @@ __device__ inline int bitrev6(int l) {
 
 // ---- loads of 4 consecutive elements -----------------------------------------
 
-template <bool NT>
-__device__ inline void load4(const float* __restrict__ p, int nvalid, bool vec, float (&d)[4]) {
-    if (nvalid == 4 && vec) {
-        const float4 v = load_d<NT>(reinterpret_cast<const float4*>(p));
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) d[s] = s < nvalid ? load_d<NT>(p + s) : 0.f;
-    }
-}
-template <bool NT>
-__device__ inline void load4(const double* __restrict__ p, int nvalid, bool vec, double (&d)[4]) {
-    if (nvalid == 4 && vec) {
-        const double2 v0 = load_d<NT>(reinterpret_cast<const double2*>(p));
-        const double2 v1 = load_d<NT>(reinterpret_cast<const double2*>(p) + 1);
-        d[0] = v0.x; d[1] = v0.y; d[2] = v1.x; d[3] = v1.y;
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) d[s] = s < nvalid ? load_d<NT>(p + s) : 0.0;
-    }
-}
-
-// Element-aligned 16-byte vectors: the hardware takes 16-byte accesses at any
-// 4-byte address, so code using them needs no alignment of rows.
-template <typename T> struct Vec16u;
-template <> struct Vec16u<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
-template <> struct Vec16u<double> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
-
-// Rows j .. j + R - 1 of an n x K panel into registers, zeros past the first
-// nv of them. The R K values are contiguous: whole vectors when all R are there.
-template <typename T, int R, int K>
-__device__ __forceinline__ void load_panel_rows(const T* __restrict__ P, int j, int nv, T (&b)[R][K]) {
+// Four consecutive elements of a row of D, zeros past the first nvalid.
+template <bool NT, typename T>
+__device__ inline void load4(const T* __restrict__ p, int nvalid, T (&d)[4]) {
     constexpr int VW = 16 / (int)sizeof(T);
-    static_assert((R * K) % VW == 0, "whole vectors");
-    const T* p = P + (size_t)j * K;
-    if (nv == R) {
+    typedef typename Vec16u<T>::type VecT;
+    if (nvalid == 4) {
 #pragma unroll
-        for (int v = 0; v < R * K / VW; ++v) {
-            const auto x = *reinterpret_cast<const typename Vec16u<T>::type*>(p + v * VW);
+        for (int v = 0; v < 4 / VW; ++v) {
+            const VecT* q = reinterpret_cast<const VecT*>(p + v * VW);
+            const VecT x = NT ? __builtin_nontemporal_load(q) : *q;
 #pragma unroll
-            for (int q = 0; q < VW; ++q) b[(v * VW + q) / K][(v * VW + q) % K] = x[q];
+            for (int u = 0; u < VW; ++u) d[v * VW + u] = x[u];
         }
     } else {
 #pragma unroll
-        for (int s = 0; s < R; ++s)
-#pragma unroll
-            for (int t = 0; t < K; ++t) b[s][t] = s < nv ? p[s * K + t] : T(0);
+        for (int s = 0; s < 4; ++s) d[s] = s < nvalid ? load_d<NT>(p + s) : T(0);
     }
 }
 
 template <typename T, int K> struct StreamCfg {
     // Rows per batch per wave. The batch's wave-uniform row data (2K values of
     // AL and Uf per row) live in scalar registers. The per-element cost of the
-    // reduce-scatter depends on NB * K only weakly, so smaller batches cost
-    // little, while the registers of the two batches in flight set the
-    // occupancy: NB * K ~ 16 keeps K = 5 at 127 VGPRs (4 waves per SIMD),
-    // measured 25% faster than NB * K ~ 32 (2 waves per SIMD).
+    // reduce-scatter depends on NB * K only weakly, while the registers of the
+    // two batches in flight set the occupancy. Measured over NB * K ~ 4 .. 48,
+    // whole solves: up to K = 5, 16 (4 waves per SIMD at K = 3 .. 5) is the best
+    // (10^4 x 10^4, K = 5 and 6 in turn: 1657, 1652, 1621, 1598, 1597, 1818 us at 4, 8,
+    // 12, 16, 24, 32); from K = 6 on, where 16 is one or two rows, 24 hides more of
+    // the latency than the wave it costs (24 instances of 2000 x 2000, K = 6 and 7:
+    // 4.35 -> 4.22 ms; 2 10^4 x 2 10^4, initialisation at K = 11: 10.72 -> 10.45 ms).
+    // FP64 keeps 16 words: 24 and 32 were within the spread.
     static constexpr int WORDS = (int)(sizeof(T) / 4);
-    static constexpr int NB0 = 16 / (K * WORDS);
+    static constexpr int NB0 = (WORDS == 1 && K >= 6 ? 24 : 16) / (K * WORDS);
     static constexpr int NB = NB0 < 1 ? 1 : (NB0 > 8 ? 8 : NB0);
 };
 
@@ -212,8 +185,7 @@ __device__ __forceinline__ void load_batch(const T* __restrict__ D, int64_t ldd,
     for (int b = 0; b < NB; ++b) {
         const int i = i0 + STREAM_WAVES * b;
         if (!CHECK || i < i_hi) {
-            load4<(K <= D_LOADS_NT_KMAX && sizeof(T) == 4)>(D + (size_t)i * ldd + jb, FULL ? STREAM_CPL : nvalid,
-                                                             FULL, d[b]);
+            load4<(K <= D_LOADS_NT_KMAX && sizeof(T) == 4)>(D + (size_t)i * ldd + jb, FULL ? STREAM_CPL : nvalid, d[b]);
         } else {
 #pragma unroll
             for (int s = 0; s < STREAM_CPL; ++s) d[b][s] = T(0);
@@ -274,7 +246,8 @@ __device__ __forceinline__ void compute_batch(
 }
 
 // All rows of the tile for one wave. Full batches are software-pipelined: the
-// loads of batch j+1 are issued before batch j is computed.
+// loads of batch j+1 are issued before batch j is computed. FULL: the tile's
+// 256 columns are all inside the matrix.
 template <typename T, int K, bool REBUILD, bool FULL>
 __device__ __forceinline__ void stream_rows(
     const T* __restrict__ D, int64_t ldd, const T* __restrict__ AL, const T* __restrict__ Uf,
@@ -284,22 +257,20 @@ __device__ __forceinline__ void stream_rows(
     constexpr int NB = StreamCfg<T, K>::NB;
     constexpr int STEP = STREAM_WAVES * NB;
     int i0 = i_first;
-    if constexpr (FULL) {
-        if (i0 + STREAM_WAVES * (NB - 1) < i_hi) {
-            T cur[NB][STREAM_CPL], nxt[NB][STREAM_CPL];
-            load_batch<T, K, true, false>(D, ldd, i0, i_hi, jb, nvalid, nxt);
-            for (;;) {
+    if (i0 + STREAM_WAVES * (NB - 1) < i_hi) {
+        T cur[NB][STREAM_CPL], nxt[NB][STREAM_CPL];
+        load_batch<T, K, FULL, false>(D, ldd, i0, i_hi, jb, nvalid, nxt);
+        for (;;) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int s = 0; s < STREAM_CPL; ++s) cur[b][s] = nxt[b][s];
-                const int i1 = i0 + STEP;
-                const bool more = i1 + STREAM_WAVES * (NB - 1) < i_hi;
-                if (more) load_batch<T, K, true, false>(D, ldd, i1, i_hi, jb, nvalid, nxt);
-                compute_batch<T, K, REBUILD, false>(cur, AL, Uf, i0, i_hi, zeta, bl, vt, y2, res, amax, P1t, lane);
-                i0 = i1;
-                if (!more) break;
-            }
+                for (int s = 0; s < STREAM_CPL; ++s) cur[b][s] = nxt[b][s];
+            const int i1 = i0 + STEP;
+            const bool more = i1 + STREAM_WAVES * (NB - 1) < i_hi;
+            if (more) load_batch<T, K, FULL, false>(D, ldd, i1, i_hi, jb, nvalid, nxt);
+            compute_batch<T, K, REBUILD, false>(cur, AL, Uf, i0, i_hi, zeta, bl, vt, y2, res, amax, P1t, lane);
+            i0 = i1;
+            if (!more) break;
         }
     }
     for (; i0 < i_hi; i0 += STEP) {
@@ -339,23 +310,22 @@ __global__ __launch_bounds__(STREAM_THREADS) void k_stream(
     const int nvalid = min(max(g.n - jb, 0), STREAM_CPL);
 
     T bl[STREAM_CPL][K], vt[STREAM_CPL][K], y2[STREAM_CPL][K];
+    if constexpr (REBUILD) load_panel_rows<T, STREAM_CPL, K>(BL, jb, nvalid, bl);
+    load_panel_rows<T, STREAM_CPL, K>(Vf, jb, nvalid, vt);
 #pragma unroll
-    for (int s = 0; s < STREAM_CPL; ++s) {
+    for (int s = 0; s < STREAM_CPL; ++s)
 #pragma unroll
         for (int t = 0; t < K; ++t) {
-            const bool ok = s < nvalid;
-            bl[s][t] = (REBUILD && ok) ? BL[(size_t)(jb + s) * K + t] : T(0);
-            vt[s][t] = ok ? Vf[(size_t)(jb + s) * K + t] : T(0);
+            if constexpr (!REBUILD) bl[s][t] = T(0);
             y2[s][t] = T(0);
         }
-    }
 
     const int i_lo = rt * g.TM;
     const int i_hi = min(g.m, i_lo + g.TM);
     double res = 0.0;
     T amax = T(0);
     Acc* P1t = P1 + (size_t)ct * g.m * K;
-    const bool full = g.vec_ok && (ct + 1) * STREAM_TN <= g.n;   // uniform per workgroup
+    const bool full = (ct + 1) * STREAM_TN <= g.n;   // uniform per workgroup
     if (full)
         stream_rows<T, K, REBUILD, true>(D, g.ldd, AL, Uf, i_lo + wave, i_hi, jb, nvalid, zeta, bl, vt, y2, res,
                                          amax, P1t, lane);
@@ -534,7 +504,6 @@ hipError_t stream_dispatch(const StreamArgs& a, int K, hipStream_t s) {
     geom.TM = a.TM;
     geom.n_ct = a.n_ct;
     geom.n_rt = a.n_rt;
-    geom.vec_ok = a.vec_ok;
     geom.body = a.body;
     geom.post_gpart = a.post_gpart;
     geom.post_small = a.post_small;

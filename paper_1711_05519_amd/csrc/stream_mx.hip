@@ -58,8 +58,8 @@ __device__ inline __bf16 to_bf16(float x) { return static_cast<__bf16>(x); }
 __device__ inline uint16_t bf16_bits(float x) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(x)); }
 
 // NBT rows x 4 columns of D for one lane (zeros outside the matrix).
-// FULL: the tile's 256 columns are inside D and rows are 16-byte aligned, so
-// only the (wave-uniform) row bound is checked.
+// FULL: the tile's 256 columns are inside D, so only the (wave-uniform) row bound
+// is checked.
 template <int NBT, bool FULL, bool NT>
 __device__ inline void mx_load_batch(const float* __restrict__ D, int64_t ldd, int i0, int i_hi, int jb, int nvalid,
                                      float (&d)[NBT][4]) {
@@ -69,8 +69,9 @@ __device__ inline void mx_load_batch(const float* __restrict__ D, int64_t ldd, i
         const float* p = D + (size_t)i * ldd + jb;
         if constexpr (FULL) {
             if (i < i_hi) {
-                const float4 v = load_d<NT>(reinterpret_cast<const float4*>(p));
-                d[b][0] = v.x; d[b][1] = v.y; d[b][2] = v.z; d[b][3] = v.w;
+                typedef Vec16u<float>::type f4;
+                const f4 v = NT ? __builtin_nontemporal_load(reinterpret_cast<const f4*>(p)) : *reinterpret_cast<const f4*>(p);
+                d[b][0] = v[0]; d[b][1] = v[1]; d[b][2] = v[2]; d[b][3] = v[3];
             } else {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) d[b][s] = 0.f;
@@ -266,16 +267,20 @@ __global__ __launch_bounds__(STREAM_THREADS) void k_stream_mx(
     __syncthreads();
 
     float bl[4][K];
+    if constexpr (REBUILD) {
+        load_panel_rows<float, 4, K>(BL, jb, nvalid, bl);
+    } else {
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int t = 0; t < K; ++t) bl[s][t] = (REBUILD && s < nvalid) ? BL[(size_t)(jb + s) * K + t] : 0.f;
+            for (int t = 0; t < K; ++t) bl[s][t] = 0.f;
+    }
     f32x4 acc2[4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) acc2[st] = f32x4{0.f, 0.f, 0.f, 0.f};
     double res = 0.0;
     float amax = 0.f;
-    const bool full = g.vec_ok && c0 + STREAM_TN <= g.n;   // uniform per workgroup
+    const bool full = c0 + STREAM_TN <= g.n;   // uniform per workgroup
     if (full)
         mx_tile<K, REBUILD, true>(D, AL, Uf, P1, g, zeta, ct, i_lo, i_hi, wave, lane, jb, nvalid, bl, acc2, vl, zbuf,
                                   ul, res, amax);
@@ -323,7 +328,6 @@ hipError_t mx_dispatch(const StreamArgs& a, int K, hipStream_t s) {
     geom.TM = a.TM;
     geom.n_ct = a.n_ct;
     geom.n_rt = a.n_rt;
-    geom.vec_ok = a.vec_ok;
     geom.body = a.body;
     geom.post_gpart = a.post_gpart;
     geom.post_small = a.post_small;
