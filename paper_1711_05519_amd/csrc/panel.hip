@@ -4,10 +4,9 @@
 // Row phases run one thread per row (four lanes per row in the gather) over
 // the m rows of the U side and the n rows of the V side in one grid. Sums over
 // rows (Grams, U_f^T Y1) are written as per-workgroup partials; the workgroup
-// that arrives last (atomic counter + device-scope fences) keeps a single wave
-// that sums them in a fixed order and runs the small dense algebra with
-// wave-level synchronisation only, so results are deterministic and the
-// serial tail has no block barriers.
+// that arrives last (atomic counter + device-scope fences) sums them in a fixed
+// order, so results are deterministic, and its first waves run the small dense
+// algebra: factorisations in one wave (the SVD in two), products in all of them.
 //
 // Notation (iteration k; K = r in the loop and K = p in the initialisation):
 //   U_f, V_f   bases read by the streaming pass (dtype of D)
@@ -99,8 +98,9 @@ __device__ __forceinline__ void rows_outer_sum(const double (&a)[K], const doubl
 }
 
 // Two such sums with a shared right factor in one pass: dst1 = sum a1 (x) b,
-// dst2 = sum a2 (x) b. sa1, sa2, sb: LDS scratch of NR*K doubles each.
-template <int K, int NR, int NT>
+// dst2 = sum a2 (x) b. sa1, sa2, sb: LDS scratch of NR*K doubles each. SYM2: a2 is
+// b, and only the entries of dst2 on and above the diagonal are written.
+template <int K, int NR, int NT, bool SYM2 = false>
 __device__ __forceinline__ void rows_outer_sum2(const double (&a1)[K], const double (&a2)[K], const double (&b)[K],
                                                 bool writer, int slot, double* sa1, double* sa2, double* sb,
                                                 double* __restrict__ dst1, double* __restrict__ dst2) {
@@ -135,7 +135,7 @@ __device__ __forceinline__ void rows_outer_sum2(const double (&a1)[K], const dou
         for (; r < NR; r += G) c0 = fma(sa[r * K + t1], sb[r * K + t2], c0);
         double acc = (c0 + c1) + (c2 + c3);
         acc = group_sum<G>(acc);
-        if (sub == 0 && x0 < E) (second ? dst2 : dst1)[e] = acc;
+        if (sub == 0 && x0 < E && !(SYM2 && second && t1 > t2)) (second ? dst2 : dst1)[e] = acc;
     }
     __syncthreads();
 }
@@ -174,24 +174,46 @@ __device__ __forceinline__ double w_mlp(const float* __restrict__ th, const doub
 
 // ---- the 2K x 2K step shared by the FP32 gather and the FP64 complement ------
 //
-// Single wave (a second one, in jacobi_right, takes the right singular vectors).
-// Given C*, C2, the Grams G1 = W1^T W1 and G2 = W2^T W2 and
-// R_U^{-1}, R_V^{-1}: R1, R2 by Cholesky, M = [[C*, R2^T], [R1, 0]], its SVD,
-// then either the next threshold (Algorithm 1) or the convergence test of the
-// initial subspace iteration, and the coefficients of the new factors
+// The first TAIL_WAVES waves of the last workgroup. Given C*, C2, the Grams
+// G1 = W1^T W1 and G2 = W2^T W2 and R_U^{-1}, R_V^{-1}: R1, R2 by Cholesky,
+// M = [[C*, R2^T], [R1, 0]], its SVD, then either the next threshold
+// (Algorithm 1) or the convergence test of the initial subspace iteration, and
+// the coefficients of the new factors
 //   U_{k+1} = U_f E1 + S_U E2,   V_{k+1} = V_f F1 + S_V F2,
-// with (S_U, S_V) = (Y1, Y2) when gram_form, (W1, W2) otherwise.
+// with (S_U, S_V) = (Y1, Y2) when gram_form, (W1, W2) otherwise. The
+// factorisations run in one wave (the SVD in two), the products in all; the
+// threshold (wave 0) and the coefficients (the others) do not wait for each other.
+constexpr int TAIL_WAVES = 4;
+constexpr int TAIL_THREADS = TAIL_WAVES * WAVE;
+
+// sum_l A[i][l] B[l][j] and sum_l A[l][i] B[l][j] for K x K matrices (ld K, LDS)
+template <int K> __device__ __forceinline__ double dot_nn(const double* A, const double* B, int i, int j) {
+    double v = 0.0;
+#pragma unroll(K <= 8 ? K : 4)
+    for (int l = 0; l < K; ++l) v = fma(A[i * K + l], B[l * K + j], v);
+    return v;
+}
+template <int K> __device__ __forceinline__ double dot_tn(const double* A, const double* B, int i, int j) {
+    double v = 0.0;
+#pragma unroll(K <= 8 ? K : 4)
+    for (int l = 0; l < K; ++l) v = fma(A[l * K + i], B[l * K + j], v);
+    return v;
+}
+
 template <int K>
-__device__ __forceinline__ void w_svd_tail(const PanelArgs& a, Ctrl* ctrl, const double* cs, const double* c2,
-                           const double* g1, const double* g2, const double* ru, const double* rv,
-                           bool gram_form, const float* th, bool th_lds, JacobiLds<2 * K>* jac, double* Vm) {
+__device__ __forceinline__ void svd_tail(const PanelArgs& a, Ctrl* ctrl, const double* cs, const double* c2,
+                                         const double* g1, const double* g2, const double* ru, const double* rv,
+                                         bool gram_form, const float* th, bool th_lds) {
     constexpr int N = 2 * K;
     __shared__ double r1[K * K], r1i[K * K], r2[K * K], r2i[K * K];
-    __shared__ double Ma[N * N], Um[N * N], sg[N];
-    __shared__ double x1[K * K], x2[K * K], z1[K * K], z2[K * K], t1[K * K], t2[K * K];
-    const int lane = lane_id();
-    w_chol_inv2<K>(g1, r1, r1i, g2, r2, r2i);
-    for (int e = lane; e < N * N; e += WAVE) {
+    __shared__ double Ma[N * N], Um[N * N], Vm[N * N], sg[N];
+    __shared__ double x1[K * K], x2[K * K], z1[K * K], z2[K * K];
+    __shared__ JacobiLds<N> jac;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    if (wave == 0) w_chol_inv2<K>(g1, r1, r1i, g2, r2, r2i);
+    __syncthreads();
+    for (int e = tid; e < N * N; e += TAIL_THREADS) {
         const int col = e / N, rw = e % N;
         double v = 0.0;
         if (rw < K && col < K) v = cs[rw * K + col];
@@ -199,54 +221,55 @@ __device__ __forceinline__ void w_svd_tail(const PanelArgs& a, Ctrl* ctrl, const
         else if (col < K) v = r1[(rw - K) * K + col];         // R1
         Ma[e] = v;
     }
-    wave_sync();
+    __syncthreads();
     // Pairs of columns with ||a||^2 <= sigma_dead^2 ||M||_F^2 / N <= (sigma_dead
     // sigma_1)^2 are not rotated against each other: both end below the
     // dropping level below, and such a rotation moves no other column.
     const double neg2 = ctrl->sigma_dead * ctrl->sigma_dead / N;
-    const int sweeps = jacobi_left<N, true>(Ma, sg, Um, jac, neg2, ctrl->single ? JACOBI_QUAD_F32 : JACOBI_QUAD);
+    const int sweeps =
+        jacobi_svd<N, true>(wave, Ma, sg, Um, Vm, &jac, neg2, ctrl->single ? JACOBI_QUAD_F32 : JACOBI_QUAD);
     // Triplets whose singular value is at the rounding level of the products
     // (sigma_j <= sigma_dead * sigma_1) carry no information about the range
     // of P_T(Z): their vectors are noise and need not be orthogonal to U*, so
     // they are dropped (zero columns) instead of entering the next basis.
     const double cut = ctrl->sigma_dead * sg[0];
-    for (int e = lane; e < N * N; e += WAVE) {
-        if (sg[e / N] <= cut) { Um[e] = 0.0; Vm[e] = 0.0; }
-    }
-    wave_sync();
     // X1 = U_M[:K, :K], X2 = R1^{-1} U_M[K:, :K]; Z1, Z2 likewise from V_M
-    for (int e = lane; e < K * K; e += WAVE) {
+    for (int x = tid; x < 2 * K * K; x += TAIL_THREADS) {
+        const bool right = x >= K * K;
+        const int e = right ? x - K * K : x;
         const int i = e / K, j = e % K;   // coefficient row i, singular triplet j
-        double xx = 0.0, zz = 0.0;
-        for (int l = 0; l < K; ++l) {
-            xx = fma(r1i[i * K + l], Um[j * N + K + l], xx);
-            zz = fma(r2i[i * K + l], Vm[j * N + K + l], zz);
-        }
-        x1[e] = Um[j * N + i];
-        z1[e] = Vm[j * N + i];
-        x2[e] = xx;
-        z2[e] = zz;
+        const double* X = (right ? Vm : Um) + j * N;
+        const double* Ri = right ? r2i : r1i;
+        double v = 0.0;
+#pragma unroll(K <= 8 ? K : 4)
+        for (int l = 0; l < K; ++l) v = fma(Ri[i * K + l], X[K + l], v);
+        const bool live = sg[j] > cut;
+        (right ? z1 : x1)[e] = live ? X[i] : 0.0;
+        (right ? z2 : x2)[e] = live ? v : 0.0;
     }
-    wave_sync();
+    __syncthreads();
+    if (gram_form) {   // X1 - C* X2 and Z1 - C2 Z2, in place
+        for (int x = tid; x < 2 * K * K; x += TAIL_THREADS) {
+            const bool right = x >= K * K;
+            const int e = right ? x - K * K : x;
+            const double v = dot_nn<K>(right ? c2 : cs, right ? z2 : x2, e / K, e % K);
+            (right ? z1 : x1)[e] -= v;
+        }
+        __syncthreads();
+    }
     Small* sm = a.small;
-    if (gram_form) {
-        // E1 = R_U^{-1} (X1 - C* X2), E2 = R_V^{-1} X2, F1 = R_V^{-1} (Z1 - C2 Z2), F2 = R_U^{-1} Z2
-        w_mm2<K, false>(cs, x2, t1, c2, z2, t2);
-        for (int e = lane; e < K * K; e += WAVE) { t1[e] = x1[e] - t1[e]; t2[e] = z1[e] - t2[e]; }
-        wave_sync();
-        w_mm2<K, false>(ru, t1, x1, rv, t2, z1);
-        w_mm2<K, false>(rv, x2, t1, ru, z2, t2);
-        w_store<K>(x1, sm->E1);
-        w_store<K>(t1, sm->E2);
-        w_store<K>(z1, sm->F1);
-        w_store<K>(t2, sm->F2);
-    } else {
-        // E1 = R_U^{-1} X1, E2 = X2, F1 = R_V^{-1} Z1, F2 = Z2
-        w_mm2<K, false>(ru, x1, t1, rv, z1, t2);
-        w_store<K>(t1, sm->E1);
-        w_store<K>(x2, sm->E2);
-        w_store<K>(t2, sm->F1);
-        w_store<K>(z2, sm->F2);
+    if (wave > 0) {
+        // gram_form: E1 = R_U^{-1} (X1 - C* X2), E2 = R_V^{-1} X2, F1 = R_V^{-1} (Z1 - C2 Z2), F2 = R_U^{-1} Z2;
+        // otherwise: E1 = R_U^{-1} X1, E2 = X2, F1 = R_V^{-1} Z1, F2 = Z2
+        for (int x = tid - WAVE; x < 4 * K * K; x += TAIL_THREADS - WAVE) {
+            const int q = x / (K * K), e = x % (K * K), i = e / K, j = e % K;
+            double v;
+            if (q < 2) v = dot_nn<K>(q ? rv : ru, q ? z1 : x1, i, j);
+            else if (gram_form) v = dot_nn<K>(q == 2 ? rv : ru, q == 2 ? x2 : z2, i, j);
+            else v = q == 2 ? x2[e] : z2[e];
+            (q == 0 ? sm->E1 : q == 1 ? sm->F1 : q == 2 ? sm->E2 : sm->F2)[i * KMAX + j] = v;
+        }
+        return;
     }
     if (lane < N) sm->sigma_M[lane] = sg[lane];
     if (lane < K) sm->sigma_new[lane] = sg[lane];
@@ -381,7 +404,9 @@ __device__ inline PanelArgs at_instance(const PanelArgs& a0) {
 
 // The last workgroup sums the per-workgroup partials with all its threads.
 // FP32 (gram_form): also the Grams of Y1 and Y2, and the whole 2K x 2K step in
-// the tail. FP64: only C* and C2; the complement kernel forms W explicitly.
+// the tail. (The products by one wave took 2.9 us of the tail at K = 6 and 10 at
+// K = 11, the coefficients of the factors 2.0 and 5.0; by four waves 1.3 and 3.5,
+// and 0.4 and 1.0.) FP64: only C* and C2; the complement kernel forms W explicitly.
 template <typename T, int K, int NT>
 __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
     PanelArgs a = at_instance(a_);
@@ -518,14 +543,14 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
     double* gp = a.gpart + (size_t)blockIdx.x * GPART_STRIDE;
     const bool writer = chunk == 0;   // y and f are zero unless this lane holds a valid row
     if (GRAM)   // U_f^T Y1 (V_f^T Y2) and Gram(Y1) (Gram(Y2))
-        rows_outer_sum2<K, RPB, NT>(f, y, y, writer, slot, sa, shbuf + 2 * FB, sb, gp, gp + KMAX * KMAX);
+        rows_outer_sum2<K, RPB, NT, true>(f, y, y, writer, slot, sa, shbuf + 2 * FB, sb, gp, gp + KMAX * KMAX);
     else
         rows_outer_sum<K, RPB, NT>(f, y, writer, slot, sa, sb, gp);   // U_f^T Y1 or V_f^T Y2
     if (!last_block_arrives(&ctrl->cnt[CNT_GATHER], &flag)) return;
 
     // ---- last workgroup: all threads sum the partials, then one wave ----
     __shared__ double sums[4 * K * K], ru[K * K], rv[K * K], cs[K * K], c2[K * K], tmp[K * K], tmp2[K * K];
-    __shared__ double g1[K * K], g2[K * K];
+    __shared__ double g1[K * K], g2[K * K], tmp3[K * K], tmp4[K * K];
     __shared__ double part[NT], rsum[2];
     double* craw = sums;              // U_f^T Y1
     double* craw2 = sums + K * K;     // V_f^T Y2
@@ -537,12 +562,14 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
     // are summed, so that the three loads overlap
     double rv_[RESID_LD], rw_[RESID_LD];
     block_resid_fetch<NT>(a.resid, a.n_tiles, sigma_stage, rv_, rw_);
-    double ru_pre[w_per_lane<K>()], rv_pre[w_per_lane<K>()];
-    if (threadIdx.x < WAVE) {
-        w_fetch<K>(a.small->RUinv, ru_pre);
-        w_fetch<K>(a.small->RVinv, rv_pre);
+    static_assert(K * K <= TAIL_THREADS && TAIL_THREADS <= NT, "one entry per thread of the tail");
+    double ru_pre = 0.0, rv_pre = 0.0;
+    if ((int)threadIdx.x < K * K) {
+        const int at = (threadIdx.x / K) * KMAX + threadIdx.x % K;
+        ru_pre = a.small->RUinv[at];
+        rv_pre = a.small->RVinv[at];
     }
-    // The single-wave tail works on a copy of the control block in LDS (no
+    // The tail works on a copy of the control block in LDS (no
     // other workgroup or kernel touches it meanwhile), loaded with the other
     // loads of this phase and written back whole at the end.
     constexpr int CW = (int)(sizeof(Ctrl) / 4);
@@ -561,7 +588,7 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
         const int e = threadIdx.x + u * NT;
         thv[u] = (GRAM && a.mlp && e < MLP_PARAMS) ? a.mlp[e] : 0.f;
     }
-    block_sum_partials<K * K, GRAM ? 4 : 2, NT>(a.gpart, gU, gV, sums, part);
+    block_sum_partials<K * K, GRAM ? 4 : 2, NT, 16, GRAM ? K : 0>(a.gpart, gU, gV, sums, part);
 #pragma unroll
     for (int u = 0; u < TPT; ++u) {
         const int e = threadIdx.x + u * NT;
@@ -572,27 +599,43 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
         }
     }
     block_resid<NT>(a.resid, a.n_tiles, sigma_stage, rv_, rw_, part, rsum);
-    if (threadIdx.x >= 2 * WAVE) return;
-    __shared__ JacobiLds<2 * K> jac;
-    __shared__ double Vm[4 * K * K];
-    if (threadIdx.x >= WAVE) {
-        if (GRAM) jacobi_right<2 * K>(Vm, &jac);
-        return;
-    }
-    const int lane = lane_id();
-    if (lane < CW) reinterpret_cast<uint32_t*>(&cl)[lane] = cword;
+    if (threadIdx.x >= TAIL_THREADS) return;
+    const int tid = threadIdx.x;
+    if (tid < CW) reinterpret_cast<uint32_t*>(&cl)[tid] = cword;
     Ctrl* const cg = ctrl;   // the control block in device memory
     ctrl = &cl;
-    w_put<K>(ru_pre, ru);
-    w_put<K>(rv_pre, rv);
-    // C* = R_U^{-T} (U_f^T Y1) R_V^{-1},  C2 = R_V^{-T} (V_f^T Y2) R_U^{-1}
-    w_mm2<K, false>(craw, rv, tmp, craw2, ru, tmp2);
-    w_mm2<K, true>(ru, tmp, cs, rv, tmp2, c2);
-    w_store<K>(cs, a.small->Cstar);
-    w_store<K>(c2, a.small->C2);
+    if (tid < K * K) {
+        ru[tid] = ru_pre;
+        rv[tid] = rv_pre;
+    }
+    __syncthreads();
+    // C* = R_U^{-T} (U_f^T Y1) R_V^{-1},  C2 = R_V^{-T} (V_f^T Y2) R_U^{-1}, and (gram form)
+    // G1 = R_V^{-T} Gram(Y1) R_V^{-1} - C*^T C*,  G2 = R_U^{-T} Gram(Y2) R_U^{-1} - C2^T C2:
+    // the right products, then C*, C2, then G1, G2
+    for (int x = tid; x < (GRAM ? 4 : 2) * K * K; x += TAIL_THREADS) {
+        const int q = x / (K * K), e = x % (K * K), i = e / K, j = e % K;
+        if (q < 2) {
+            (q ? tmp2 : tmp)[e] = dot_nn<K>(q ? craw2 : craw, q ? ru : rv, i, j);
+        } else {
+            const double* G = q == 2 ? gy1 : gy2;   // on and above the diagonal
+            const double* R = q == 2 ? rv : ru;
+            double v = 0.0;
+#pragma unroll(K <= 8 ? K : 4)
+            for (int l = 0; l < K; ++l) v = fma(G[i <= l ? i * K + l : l * K + i], R[l * K + j], v);
+            (q == 2 ? tmp3 : tmp4)[e] = v;
+        }
+    }
+    __syncthreads();
+    for (int x = tid; x < 2 * K * K; x += TAIL_THREADS) {
+        const int q = x / (K * K), e = x % (K * K), i = e / K, j = e % K;
+        const double v = dot_tn<K>(q ? rv : ru, q ? tmp2 : tmp, i, j);
+        (q ? c2 : cs)[e] = v;
+        if (!GRAM) (q ? a.small->C2 : a.small->Cstar)[i * KMAX + j] = v;   // for the complement kernel
+    }
+    const int lane = lane_id();
     const double rs = rsum[0], mx = rsum[1];
-    int go_on = 0;
-    if (lane == 0) {
+    __shared__ int go_on;
+    if (tid == 0) {
         ctrl->resid2 = rs;
         if (sigma_stage) {
             ctrl->normD2 = rs;   // zeta = +inf: the residual is ||D||_F^2
@@ -628,19 +671,17 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
         ctrl->post_update = 0;   // gpart now holds the gather's partials
         go_on = (GRAM && a.mode == GATHER_WITH_SVD && ctrl->active) ? 1 : 0;
     }
-    go_on = __shfl(go_on, 0, WAVE);
-    wave_sync();
-    if (go_on) {
-        // G1 = R_V^{-T} Gram(Y1) R_V^{-1} - C*^T C*,  G2 = R_U^{-T} Gram(Y2) R_U^{-1} - C2^T C2
-        w_mm2<K, false>(gy1, rv, tmp, gy2, ru, tmp2);
-        w_mm2<K, true>(rv, tmp, g1, ru, tmp2, g2);
-        w_mm2<K, true>(cs, cs, craw, c2, c2, craw2);
-        for (int e = lane; e < K * K; e += WAVE) { g1[e] -= craw[e]; g2[e] -= craw2[e]; }
-        wave_sync();
-        w_svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, true, a.mlp ? th_s : nullptr, true, &jac, Vm);
-    } else if (GRAM) {
-        jacobi_none<2 * K>(&jac);
+    __syncthreads();
+    if (GRAM && go_on) {
+        for (int x = tid; x < 2 * K * K; x += TAIL_THREADS) {
+            const int q = x / (K * K), e = x % (K * K), i = e / K, j = e % K;
+            const double* c = q ? c2 : cs;
+            (q ? g2 : g1)[e] = dot_tn<K>(q ? ru : rv, q ? tmp4 : tmp3, i, j) - dot_tn<K>(c, c, i, j);
+        }
+        __syncthreads();
+        svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, true, a.mlp ? th_s : nullptr, true);
     }
+    if (tid >= WAVE) return;
     wave_sync();
     if (lane < CW) reinterpret_cast<uint32_t*>(cg)[lane] = reinterpret_cast<const uint32_t*>(&cl)[lane];
 }
@@ -692,15 +733,9 @@ __global__ __launch_bounds__(PANEL_THREADS) void k_complement(PanelArgs a_) {
     double* g1 = gg;
     double* g2 = gg + K * K;
     block_sum_partials<K * K, 2, PANEL_THREADS>(a.gpart, a.gU, a.gV, gg, part);
-    if (threadIdx.x >= 2 * WAVE) return;
-    __shared__ JacobiLds<2 * K> jac;
-    __shared__ double Vm[4 * K * K];
-    if (threadIdx.x >= WAVE) {
-        jacobi_right<2 * K>(Vm, &jac);
-        return;
-    }
-    if (lane_id() == 0) ctrl->cnt[CNT_COMPLEMENT] = 0;
-    w_svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, false, a.mlp, false, &jac, Vm);
+    if (threadIdx.x == 0) ctrl->cnt[CNT_COMPLEMENT] = 0;
+    static_assert(PANEL_THREADS == TAIL_THREADS, "the whole workgroup takes part in the tail");
+    svd_tail<K>(a, ctrl, cs, c2, g1, g2, ru, rv, false, a.mlp, false);
 }
 
 // ---- kernel 3: new factors (or entry from a given state), Trim, new bases ----

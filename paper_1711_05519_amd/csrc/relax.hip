@@ -119,7 +119,7 @@ template <int K> struct RelaxTail {
     static __device__ __forceinline__ void stage2(const Args& a) {
         constexpr int N = K2;
         __shared__ double RG[2][K2 * K2], Ri[2][K2 * K2], GG[2][K2 * K2];
-        __shared__ double ra[2][K * K];
+        __shared__ double ra[2][K * K], cb[2][K2];
         __shared__ double Um[N * N], Vm[N * N], sg[N];
         __shared__ JacobiLds<N> jac;
         __shared__ double dM[K3 * K3], A1[K3 * K], EL[N * K], A2[K * K3], ET[K * K3];
@@ -136,7 +136,7 @@ template <int K> struct RelaxTail {
             ra[side][i] = a.Rinv[side][(i / K) * KMAX + i % K];
         }
         __syncthreads();
-        if (tid < WAVE) w_chol_inv2<K2>(GG[0], RG[0], Ri[0], GG[1], RG[1], Ri[1]);
+        if (tid < 2 * WAVE) chol_group<K2>(GG[tid / WAVE], RG[tid / WAVE], Ri[tid / WAVE], cb[tid / WAVE], lane_id());
         __syncthreads();
         // M (leading block, column-major, into GG[0], free now) and dM (row-major)
         double* M = GG[0];

@@ -280,8 +280,10 @@ __device__ __forceinline__ void stream_rows(
     }
 }
 
+// Waves per SIMD of the initialisation's FP32 pass at K = 15: the closing sums of an
+// update (pass_finishes_update) must not cost the pass one.
 template <typename T, int K, bool REBUILD>
-__global__ __launch_bounds__(STREAM_THREADS) void k_stream(
+__global__ __launch_bounds__(STREAM_THREADS, (sizeof(T) == 4 && !REBUILD && K == 15) ? 3 : 1) void k_stream(
     const T* __restrict__ D, const T* __restrict__ AL, const T* __restrict__ BL, const T* __restrict__ Uf,
     const T* __restrict__ Vf, typename AccOf<T>::type* __restrict__ P1, typename AccOf<T>::type* __restrict__ P2,
     double* __restrict__ resid, Ctrl* __restrict__ ctrl, StreamGeom g) {

@@ -213,8 +213,10 @@ __device__ inline void mx_tile(const float* __restrict__ D, const float* __restr
     }
 }
 
+// Waves per SIMD: the closing sums of an update (pass_finishes_update) must not
+// cost the pass one.
 template <int K, bool REBUILD>
-__global__ __launch_bounds__(STREAM_THREADS) void k_stream_mx(
+__global__ __launch_bounds__(STREAM_THREADS, K <= 11 ? 4 : K <= 14 ? 3 : 2) void k_stream_mx(
     const float* __restrict__ D, const float* __restrict__ AL, const float* __restrict__ BL,
     const float* __restrict__ Uf, const float* __restrict__ Vf, float* __restrict__ P1, float* __restrict__ P2,
     double* __restrict__ resid, Ctrl* __restrict__ ctrl, StreamGeom g) {

@@ -1,7 +1,6 @@
 // Single-wave and whole-workgroup helpers of the small FP64 algebra: LDS
-// matrix moves and products, fixed-order sums of per-workgroup partials, a
-// two-at-once Cholesky factorisation with inverses, and a one-sided Jacobi
-// SVD run by one wave. Shared by the panel kernels of the loop and of the
+// matrix moves, fixed-order sums of per-workgroup partials, a Cholesky
+// factorisation with inverse, and a one-sided Jacobi SVD run by two waves. Shared by the panel kernels of the loop and of the
 // relaxed iteration.
 #pragma once
 
@@ -47,54 +46,6 @@ __device__ inline void w_store(const double* s, double* __restrict__ g) {
     for (int e = lane_id(); e < K * K; e += WAVE) g[(e / K) * KMAX + (e % K)] = s[e];
     wave_sync();
 }
-// Global -> registers -> LDS in two steps, so that the load can be issued
-// early and its latency overlap other work: lane l holds entries l, l + WAVE, ...
-template <int K> constexpr int w_per_lane() { return (K * K + WAVE - 1) / WAVE; }
-template <int K>
-__device__ inline void w_fetch(const double* __restrict__ g, double (&v)[w_per_lane<K>()]) {
-#pragma unroll
-    for (int u = 0; u < w_per_lane<K>(); ++u) {
-        const int e = lane_id() + u * WAVE;
-        v[u] = e < K * K ? g[(e / K) * KMAX + (e % K)] : 0.0;
-    }
-}
-template <int K>
-__device__ inline void w_put(const double (&v)[w_per_lane<K>()], double* s) {
-#pragma unroll
-    for (int u = 0; u < w_per_lane<K>(); ++u) {
-        const int e = lane_id() + u * WAVE;
-        if (e < K * K) s[e] = v[u];
-    }
-    wave_sync();
-}
-// C = op(A) B (K x K, ld K, LDS); op = transpose when TA
-template <int K, bool TA>
-__device__ inline void w_mm(const double* A, const double* B, double* C) {
-    for (int e = lane_id(); e < K * K; e += WAVE) {
-        const int i = e / K, j = e % K;
-        double acc = 0.0;
-        for (int l = 0; l < K; ++l) acc = fma(TA ? A[l * K + i] : A[i * K + l], B[l * K + j], acc);
-        C[e] = acc;
-    }
-    wave_sync();
-}
-// Two independent products C = op(A) B and F = op(D) E in one pass
-template <int K, bool TA>
-__device__ inline void w_mm2(const double* A, const double* B, double* C, const double* D, const double* E,
-                             double* F) {
-    for (int x = lane_id(); x < 2 * K * K; x += WAVE) {
-        const bool second = x >= K * K;
-        const int e = second ? x - K * K : x;
-        const double* P = second ? D : A;
-        const double* Q = second ? E : B;
-        const int i = e / K, j = e % K;
-        double acc = 0.0;
-        for (int l = 0; l < K; ++l) acc = fma(TA ? P[l * K + i] : P[i * K + l], Q[l * K + j], acc);
-        (second ? F : C)[e] = acc;
-    }
-    wave_sync();
-}
-
 // Sums of the per-workgroup partials of a kernel whose first gU workgroups
 // cover the U side (rows of m) and the next gV the V side (rows of n). Job j
 // sums entry e < E of the partial at offset (j / 2) * KMAX^2 of every
@@ -105,7 +56,9 @@ __device__ inline void w_mm2(const double* A, const double* B, double* C, const 
 // added in order of s. Up to L loads per thread are in flight at once, so a
 // round over up to L S partials costs one memory latency. part: NT doubles
 // of LDS.
-template <int E, int J, int NT, int L = 16>
+// SYM > 0: jobs 2 and up are symmetric SYM x SYM matrices of which only the
+// entries on and above the diagonal are there (and are summed).
+template <int E, int J, int NT, int L = 16, int SYM = 0>
 __device__ __forceinline__ void block_sum_partials(const double* __restrict__ gpart, int gU, int gV, double* out, double* part) {
     constexpr int PAIRS = J * E;
     constexpr int PR = PAIRS >= NT ? NT : PAIRS;   // pairs per round
@@ -115,8 +68,8 @@ __device__ __forceinline__ void block_sum_partials(const double* __restrict__ gp
     for (int q0 = 0; q0 < PAIRS; q0 += PR) {
         const int sp = t / PR, q = q0 + t % PR;
         double acc = 0.0;
-        if (sp < S && q < PAIRS) {
-            const int j = q / E, e = q - (q / E) * E;
+        const int j = q / E, e = q - (q / E) * E;
+        if (sp < S && q < PAIRS && !(SYM > 0 && j >= 2 && e / (SYM > 0 ? SYM : 1) > e % (SYM > 0 ? SYM : 1))) {
             const int first = (j & 1) ? gU : 0, count = (j & 1) ? gV : gU;
             const double* g = gpart + (size_t)first * GPART_STRIDE + (j >> 1) * (KMAX * KMAX) + e;
             for (int b0 = sp; b0 < count; b0 += L * S) {
@@ -209,58 +162,48 @@ __device__ inline double readlane64(double x, int l) {
     return __longlong_as_double((int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
-// Two Cholesky factorisations at once, G0 = R0^T R0 in lanes 0..31 and
-// G1 = R1^T R1 in lanes 32..63, with the inverses R^{-1} (all K x K, ld K,
-// LDS; R upper triangular). Lane c of a half owns column c in registers; the
-// factorisation is right-looking: at step j the pivot and row j of R are
-// formed in registers and broadcast with readlane, and the trailing columns
-// are updated. A pivot that vanishes (d <= CHOL_DEAD_REL * G_jj, or G_jj ~ 0)
-// marks a numerically dependent column: its row of R and column of R^{-1}
-// are 0. R^{-1} by back substitution from R in LDS, column c in lane c.
+// Cholesky factor and its inverse of a K x K matrix G = R^T R (all K x K, ld K,
+// LDS; R upper triangular) by the lanes c of a group of a wave: lane c < K owns
+// column c of G, lane K + c column c of the identity, in registers. Step j
+// leaves row j of R in the first, row j of R^{-T} in the second (forward
+// elimination of [G | I]), so the inverse needs no pass of its own. Row j of the
+// reduced matrix is handed round through LDS (buf, K values): one write and one
+// read per step instead of a broadcast by lane per entry (two at K = 11: 7.4 ->
+// 3.6 us). A pivot that vanishes (d <= CHOL_DEAD_REL * G_jj, or G_jj ~ 0) marks a
+// numerically dependent column: its row of R and column of R^{-1} are 0.
 template <int K>
-__device__ __forceinline__ void w_chol_inv2(const double* G0, double* R0, double* Ri0, const double* G1, double* R1,
-                            double* Ri1) {
-    static_assert(K <= 32, "one column per lane of a half wave");
-    const int lane = lane_id();
-    const int h = lane >> 5, c = lane & 31;
-    const double* G = h ? G1 : G0;
-    double g[K], r[K], inv[K], x[K];
+__device__ __forceinline__ void chol_group(const double* G, double* R, double* Ri, double* buf, int c) {
+    double a[K];
 #pragma unroll
-    for (int i = 0; i < K; ++i) g[i] = c < K ? G[i * K + c] : 0.0;
+    for (int i = 0; i < K; ++i) a[i] = c < K ? G[i * K + c] : (c - K == i ? 1.0 : 0.0);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const double d = h ? readlane64(g[j], 32 + j) : readlane64(g[j], j);
+        if (c < K) buf[c] = a[j];
         const double gjj = G[j * K + j];
+        wave_sync();
+        double v[K];
+#pragma unroll
+        for (int i = j; i < K; ++i) v[i] = buf[i];
+        wave_sync();
+        const double d = v[j];
         const bool live = gjj > 1e-300 && d > CHOL_DEAD_REL * gjj;
-        const double ivj = live ? rsqrt(d) : 0.0;   // one reciprocal square root, no division
-        const double rjj = live ? d * ivj : 0.0;
-        inv[j] = ivj;
-        r[j] = (c == j) ? rjj : (c > j ? g[j] * ivj : 0.0);   // R[j][c]
+        const double iv = live ? rsqrt(d) : 0.0;   // one reciprocal square root, no division
+        const double r = c < j ? 0.0 : a[j] * iv;
+        if (c < K) R[j * K + c] = r;
+        else if (c < 2 * K) Ri[(c - K) * K + j] = a[j] * iv;
 #pragma unroll
-        for (int i = j + 1; i < K; ++i) {
-            const double rji = h ? readlane64(r[j], 32 + i) : readlane64(r[j], i);
-            g[i] = fma(-rji, r[j], g[i]);
-        }
+        for (int i = j + 1; i < K; ++i) a[i] = fma(-(v[i] * iv), a[j] * iv, a[i]);
     }
-    double* R = h ? R1 : R0;
-    double* Ri = h ? Ri1 : Ri0;
-    if (c < K) {
-#pragma unroll
-        for (int i = 0; i < K; ++i) R[i * K + c] = r[i];
-    }
-    wave_sync();
-    // back substitution with R read from LDS (same address in all lanes of a half)
-#pragma unroll
-    for (int i = K - 1; i >= 0; --i) {
-        double v = (i == c) ? 1.0 : 0.0;
-#pragma unroll
-        for (int k = i + 1; k < K; ++k) v = fma(-R[i * K + k], x[k], v);
-        x[i] = v * inv[i];
-    }
-    if (c < K) {
-#pragma unroll
-        for (int i = 0; i < K; ++i) Ri[i * K + c] = x[i];
-    }
+}
+
+// Two such factorisations by one wave (K <= 16: 2K lanes each)
+template <int K>
+__device__ __forceinline__ void w_chol_inv2(const double* G0, double* R0, double* Ri0, const double* G1, double* R1,
+                                            double* Ri1) {
+    static_assert(K <= 16, "2K lanes of a half wave per matrix");
+    __shared__ double buf[2][KMAX];
+    const int lane = lane_id(), h = lane >> 5;
+    chol_group<K>(h ? G1 : G0, h ? R1 : R0, h ? Ri1 : Ri0, buf[h], lane & 31);
     wave_sync();
 }
 
