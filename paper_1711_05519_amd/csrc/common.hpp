@@ -193,14 +193,6 @@ __device__ inline bool body_runs(const Ctrl* c, int body) {
     return true;
 }
 
-// Signals completion of this workgroup's partial results; returns true in all
-// threads of the single workgroup that finished last. Partials written by any
-// thread of any workgroup before the call are visible to that workgroup
-// afterwards. The counter is reset by the caller.
-// Thread 0 alone issues the agent-scope fences, after a workgroup barrier
-// (which completes every wave's stores at workgroup scope; the release fence
-// is cumulative over them) and before the barrier that hands the result to the
-// other waves. A fence in every wave multiplies the L2 write-backs.
 // Tile handled by workgroup b of a G-workgroup launch. Workgroups are handed to
 // the 8 XCDs of the device in turn (b, b + 8, ... on XCD b % 8); numbering the
 // tiles so that each XCD takes one contiguous run puts neighbouring tiles
@@ -275,22 +267,28 @@ template <typename X> __device__ inline X* moved(X* p, int64_t off) {
     return reinterpret_cast<X*>(reinterpret_cast<C*>(p) + off);
 }
 
-// Last-workgroup election. The workgroup barrier orders the waves but does not
-// wait for their global stores to complete (only for their LDS operations),
-// and the increment's release (agent scope: write-back of this XCD's L2, then
-// the atomic) covers what has reached the L2 by then. So every wave first
-// waits until its own stores have completed, i.e. reached the L2; otherwise
-// a partial still in flight from another wave could miss the write-back, and
-// the last workgroup, on another XCD with its own L2, would read a stale
-// value. (A release fence in every wave would also do, at 16 L2 write-backs
-// per workgroup: 17 us more per loop body at m = n = 10^4.) Only the last
-// workgroup acquires, so the others skip the L2 invalidation a full fence
-// costs.
+// Stores a partial result that the last workgroup of this launch reads: an
+// agent-scope store, which goes through this XCD's L2 to where every XCD sees it.
+__device__ inline void store_agent(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Last-workgroup election: signals that this workgroup's partial results (stored
+// with store_agent, by any of its threads) are there; returns true in all threads
+// of the single workgroup that finished last, to which all of them are visible.
+// The counter is reset by the caller. Every wave first waits until its own stores
+// have completed (the workgroup barrier alone waits only for LDS operations).
+// Since those stores went through to where all XCDs see them, the increment
+// needs no release: that writes back the XCD's whole L2, the panel rows included,
+// once for every workgroup. (A batch of 24 calls, 2000 x 2000, K = 6: 4.13 ms with
+// a release, 3.50 without; one call at 25344 x 2000, K = 2: 1.86 and 1.81.) The
+// last workgroup acquires, so that its loads of the partials miss its own caches.
+// Results written with ordinary stores are not covered: they are for later kernels.
 __device__ inline bool last_block_arrives(uint32_t* counter, int* flag_smem) {
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int last = (prev == gridDim.x - 1) ? 1 : 0;
         if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         *flag_smem = last;

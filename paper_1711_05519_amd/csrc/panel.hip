@@ -92,7 +92,7 @@ __device__ __forceinline__ void rows_outer_sum(const double (&a)[K], const doubl
         for (; r < NR; r += G) c0 = fma(sa[r * K + t1], sb[r * K + t2], c0);
         double acc = (c0 + c1) + (c2 + c3);
         acc = group_sum<G>(acc);
-        if (sub == 0 && e0 < K * K) dst[e] = acc;
+        if (sub == 0 && e0 < K * K) store_agent(dst + e, acc);
     }
     __syncthreads();
 }
@@ -135,7 +135,7 @@ __device__ __forceinline__ void rows_outer_sum2(const double (&a1)[K], const dou
         for (; r < NR; r += G) c0 = fma(sa[r * K + t1], sb[r * K + t2], c0);
         double acc = (c0 + c1) + (c2 + c3);
         acc = group_sum<G>(acc);
-        if (sub == 0 && x0 < E && !(SYM2 && second && t1 > t2)) (second ? dst2 : dst1)[e] = acc;
+        if (sub == 0 && x0 < E && !(SYM2 && second && t1 > t2)) store_agent((second ? dst2 : dst1) + e, acc);
     }
     __syncthreads();
 }
@@ -404,7 +404,7 @@ __device__ inline PanelArgs at_instance(const PanelArgs& a0) {
 
 // The last workgroup sums the per-workgroup partials with all its threads.
 // FP32 (gram_form): also the Grams of Y1 and Y2, and the whole 2K x 2K step in
-// the tail. (The products by one wave took 2.9 us of the tail at K = 6 and 10 at
+// the tail. (The products by one wave took 2.2 us of the tail at K = 6 and 4.8 at
 // K = 11, the coefficients of the factors 2.0 and 5.0; by four waves 1.3 and 3.5,
 // and 0.4 and 1.0.) FP64: only C* and C2; the complement kernel forms W explicitly.
 template <typename T, int K, int NT>

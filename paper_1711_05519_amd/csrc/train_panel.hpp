@@ -271,7 +271,7 @@ __global__ __launch_bounds__(TR_THREADS) void k_train_rows(StepArgs<typename Tai
             double v = 0.0;
 #pragma unroll
             for (int w = 0; w < TR_WAVES; ++w) v += tiles[w][at];
-            gp[e] = v;
+            store_agent(gp + e, v);
         }
     }
     if (!last_block_arrives(a.cnt, &flag)) return;
