@@ -107,12 +107,15 @@ bool status_slots_locked(DeviceInfo* d) {
     if (d->status_host) return true;
     void* h = nullptr;
     if (hipHostMalloc(&h, sizeof(HostStatus) * STATUS_SLOTS, hipHostMallocMapped | hipHostMallocCoherent) !=
-        hipSuccess)
+        hipSuccess) {
+        (void)hipGetLastError();
         return false;
+    }
     memset(h, 0, sizeof(HostStatus) * STATUS_SLOTS);
     void* dp = nullptr;
     if (hipHostGetDevicePointer(&dp, h, 0) != hipSuccess) {
         (void)hipHostFree(h);
+        (void)hipGetLastError();
         return false;
     }
     d->status_host = static_cast<HostStatus*>(h);
@@ -120,10 +123,11 @@ bool status_slots_locked(DeviceInfo* d) {
     return true;
 }
 
-// A status slot held for the duration of one call.
+// A status slot held for the duration of one call (none for a null device).
 class StatusSlot {
 public:
     explicit StatusSlot(DeviceInfo* d) : d_(d) {
+        if (!d_) return;
         std::lock_guard<std::mutex> lock(g_dev_mutex);
         if (!status_slots_locked(d_)) return;
         for (int i = 0; i < STATUS_SLOTS; ++i) {
@@ -145,6 +149,12 @@ public:
     bool ok() const { return idx_ >= 0; }
     HostStatus* host() const { return d_->status_host + idx_; }
     HostStatus* dev() const { return d_->status_dev + idx_; }
+    // for a call that can do without (its results are then copied)
+    template <typename C> void give(C* c) const {
+        if (!ok()) return;
+        c->st_host = host();
+        c->st_dev = dev();
+    }
 
 private:
     DeviceInfo* d_;
@@ -422,6 +432,7 @@ struct Ctx {
     double mixed_err;
     HostStatus* st_host = nullptr;   // the call's status slot (queues of bodies only)
     HostStatus* st_dev = nullptr;
+    mutable int32_t reports = 0;     // reports queued to the slot so far
     bool events = true;              // false: no profiler events (rpca_step_noalloc)
     int32_t batch = 1;               // instances per launch (rpca_solve_batch); all pointers are instance 0's
     int64_t slab = 0;                // bytes between the instances
@@ -690,8 +701,53 @@ int pipelined_loop(const Ctx& c, int max_bodies, Enq enqueue, Fin finished) {
     return rc;
 }
 
+// Waits until the call's last report is in its status slot; the work queued
+// before it has ended then. A kernel that writes host memory and a host that
+// polls it take 6 us, a kernel and hipStreamSynchronize 11, with a copy of the
+// results to pageable memory 22. A stream that drains without the report, or
+// reports an error, ends the wait with RPCA_EHIP.
+int wait_report(const Ctx& c) {
+    const volatile int32_t* count = &c.st_host->published;
+    auto last = std::chrono::steady_clock::now();
+    for (uint32_t spin = 1; *count != c.reports; ++spin) {
+        cpu_relax();
+        if ((spin & 1023u) != 0) continue;
+        const auto now = std::chrono::steady_clock::now();
+        if (now - last < std::chrono::microseconds(500)) continue;
+        last = now;
+        const hipError_t e = hipStreamQuery(c.s);
+        if (e == hipErrorNotReady) continue;
+        if (e == hipSuccess && *count == c.reports) break;
+        g_last_hip_error = (int)e;
+        return RPCA_EHIP;
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return RPCA_OK;
+}
+
+// The control block, after everything queued so far (through the call's status
+// slot; a call without one copies it).
 int read_ctrl(const Ctx& c, Ctrl* out) {
+    if (c.st_host) {
+        HIP_TRY(launch_publish(c.ctrl(), nullptr, nullptr, 0, c.st_dev, ++c.reports, c.s));
+        RPCA_TRY(wait_report(c));
+        memcpy(out, &c.st_host->fin, sizeof(Ctrl));
+        return RPCA_OK;
+    }
     HIP_TRY(hipMemcpyAsync(out, c.ctrl(), sizeof(Ctrl), hipMemcpyDeviceToHost, c.s));
+    HIP_TRY(hipStreamSynchronize(c.s));
+    return RPCA_OK;
+}
+
+// n doubles in device memory (at most 2 PUBLISH_HIST), in the same way.
+int read_values(const Ctx& c, const double* src, int n, double* out) {
+    if (c.st_host) {
+        HIP_TRY(launch_report(src, n, c.st_dev, ++c.reports, c.s));
+        RPCA_TRY(wait_report(c));
+        memcpy(out, &c.st_host->hist[0][0], sizeof(double) * (size_t)n);
+        return RPCA_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(out, src, sizeof(double) * (size_t)n, hipMemcpyDeviceToHost, c.s));
     HIP_TRY(hipStreamSynchronize(c.s));
     return RPCA_OK;
 }
@@ -964,17 +1020,14 @@ public:
         // entries into the status slot: one synchronisation reads them all
         if (rc_ >= 0) {
             const hipError_t le =
-                launch_publish(c_.ctrl(), c_.err_hist(), c_.zeta_hist(), p_->max_iter + 1, c_.st_dev, c_.s);
+                launch_publish(c_.ctrl(), c_.err_hist(), c_.zeta_hist(), p_->max_iter + 1, c_.st_dev, ++c_.reports, c_.s);
             if (le != hipSuccess) {
                 g_last_hip_error = (int)le;
                 rc_ = RPCA_EHIP;
             }
         }
-        hipError_t e = hipStreamSynchronize(c_.s);
-        if (e != hipSuccess && rc_ >= 0) {
-            g_last_hip_error = (int)e;
-            rc_ = RPCA_EHIP;
-        }
+        if (rc_ >= 0) rc_ = wait_report(c_) < 0 ? RPCA_EHIP : rc_;
+        if (rc_ < 0) (void)hipStreamSynchronize(c_.s);   // nothing stays in flight
         RPCA_TRY(rc_);
         const volatile HostStatus* hs = c_.st_host;
         std::atomic_thread_fence(std::memory_order_acquire);
@@ -1397,6 +1450,8 @@ int step_impl(const void* D, const rpca_params* p, rpca_state* st, void* ws, siz
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
     c.events = events;
+    StatusSlot slot(events ? c.dev : nullptr);
+    slot.give(&c);
     double nd2 = st->normD > 0 ? st->normD * st->normD : 0.0;
     if (!(nd2 > 0)) RPCA_TRY(compute_normD2(c, D, &nd2));
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, st->zeta, st->k, nd2, 0)));
@@ -1442,6 +1497,8 @@ int rpca_relaxed_step(const void* D, const rpca_params* p, rpca_state* st, doubl
     if (!is_fin(zeta) || !(zeta > 0) || !is_fin(tau) || !(tau > 0)) return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
+    StatusSlot slot(c.dev);
+    slot.give(&c);
     double nd2 = st->normD > 0 ? st->normD * st->normD : 0.0;
     if (!(nd2 > 0)) RPCA_TRY(compute_normD2(c, D, &nd2));
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, zeta, st->k, nd2, 0)));
@@ -1488,8 +1545,9 @@ int rpca_relaxed_step(const void* D, const rpca_params* p, rpca_state* st, doubl
     a.ctrl = c.ctrl();
     HIP_TRY(launch_relax(a, c.dtype, c.s));
     RelaxResult r;
-    HIP_TRY(hipMemcpyAsync(&r, a.result, sizeof(r), hipMemcpyDeviceToHost, c.s));
-    HIP_TRY(hipStreamSynchronize(c.s));
+    static_assert(sizeof(r) % sizeof(double) == 0, "read as doubles");
+    RPCA_TRY(read_values(c, reinterpret_cast<const double*>(a.result), sizeof(r) / sizeof(double),
+                         reinterpret_cast<double*>(&r)));
     out->loss = r.loss;
     out->dloss_dzeta = r.dloss_dzeta;
     out->err = r.err;
@@ -1523,6 +1581,8 @@ int rpca_unrolled_adjoint(const void* D, const rpca_params* p, int32_t K, const 
             return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
+    StatusSlot slot(c.dev);
+    slot.give(&c);
     const Layout& L = c.L;
     AdjointBufs B;
     HIP_TRY(adjoint_carve(c.ws + L.off_adj, p->m, p->n, p->r, L.rx_nct, L.rx_nrt, &B));
@@ -1555,10 +1615,9 @@ int rpca_unrolled_adjoint(const void* D, const rpca_params* p, int32_t K, const 
     P.sigma_bar = sigma_bar;
     P.V_bar = V_bar;
     HIP_TRY(adjoint_run(P, B, c.s));
-    std::vector<double> zb((size_t)K);
-    HIP_TRY(hipMemcpyAsync(zb.data(), B.zbar, sizeof(double) * (size_t)K, hipMemcpyDeviceToHost, c.s));
-    HIP_TRY(hipStreamSynchronize(c.s));
-    for (int k = 0; k < K; ++k) zeta_bar[k] = zb[(size_t)k];
+    double zb[RPCA_MAX_UNROLL];
+    RPCA_TRY(read_values(c, B.zbar, K, zb));
+    for (int k = 0; k < K; ++k) zeta_bar[k] = zb[k];
     return RPCA_OK;
 }
 
@@ -1624,6 +1683,8 @@ int rpca_tangent_products(const void* D, const rpca_params* p, const double* A_L
     if (!D || !A_L || !B_L || !U_t || !V_t || !Y1 || !Y2 || !resid2 || isnan(zeta)) return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
+    StatusSlot slot(c.dev);
+    slot.give(&c);
     const int K = p->r;
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, zeta, 0, 1.0, 0)));
     HIP_TRY(launch_convert(A_L, c.ws + c.L.off_AL, p->m * K, nullptr, K, c.dtype, c.s));

@@ -136,8 +136,10 @@ constexpr int PUBLISH_HIST = 128;
 // One per call in flight on a device (a pool in mapped, coherent host memory).
 struct HostStatus {
     BodyRecord body[BODY_RING];
-    Ctrl fin;                        // control block at the end of a solve
-    double hist[2][PUBLISH_HIST];    // err_0.., zeta_0.. at the end of a solve
+    Ctrl fin;                        // control block published by the call's last kernel
+    double hist[2][PUBLISH_HIST];    // err_0.., zeta_0.. at the end of a solve; or the
+                                     // values of a call that reports no control block
+    int32_t published;               // count of the call's reports so far, written last
 };
 
 // Small FP64 matrices shared between kernels (all K x K, row-major, ld = KMAX).

@@ -1026,8 +1026,24 @@ __global__ void k_enter_loop(Ctrl* ctrl_, int64_t slab) {
 // the err and zeta histories (at most k + 1 of them) into the call's status
 // slot in mapped host memory, so that the host reads them after one stream
 // synchronisation instead of three copies.
+// Ends a report to the host: everything this workgroup wrote to the slot is in
+// host memory before the count that the host waits for.
+__device__ inline void report_done(HostStatus* dst, int32_t count) {
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&dst->published, count, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// n doubles (at most 2 PUBLISH_HIST) into the status slot.
+__global__ void k_report(const double* src, int n, HostStatus* dst, int32_t count) {
+    double* out = &dst->hist[0][0];
+    for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = src[i];
+    report_done(dst, count);
+}
+
 __global__ void k_publish(const Ctrl* ctrl, const double* err_hist, const double* zeta_hist, int hist_n,
-                          HostStatus* dst) {
+                          HostStatus* dst, int32_t count) {
     constexpr int CW = (int)(sizeof(Ctrl) / 4);
     const uint32_t* src = reinterpret_cast<const uint32_t*>(ctrl);
     uint32_t* out = reinterpret_cast<uint32_t*>(&dst->fin);
@@ -1039,7 +1055,7 @@ __global__ void k_publish(const Ctrl* ctrl, const double* err_hist, const double
         dst->hist[0][i] = err_hist[i];
         dst->hist[1][i] = zeta_hist[i];
     }
-    __threadfence_system();
+    report_done(dst, count);
 }
 
 // Copies `bytes` (a multiple of 4) between each instance of a batch (instance
@@ -1129,9 +1145,15 @@ hipError_t launch_enter_loop(Ctrl* ctrl, int batch, int64_t slab, hipStream_t s)
 }
 
 hipError_t launch_publish(const Ctrl* ctrl, const double* err_hist, const double* zeta_hist, int hist_n,
-                          HostStatus* dst, hipStream_t s) {
+                          HostStatus* dst, int32_t count, hipStream_t s) {
     if (!dst || hist_n < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(128), 0, s, ctrl, err_hist, zeta_hist, hist_n, dst);
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(128), 0, s, ctrl, err_hist, zeta_hist, hist_n, dst, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(const double* src, int n, HostStatus* dst, int32_t count, hipStream_t s) {
+    if (!dst || n < 1 || n > 2 * PUBLISH_HIST) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, src, n, dst, count);
     return hipGetLastError();
 }
 

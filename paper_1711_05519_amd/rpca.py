@@ -142,17 +142,21 @@ def _check(status: int, where: str) -> int:
     return status
 
 
+# Addresses and sizes go to the library as integers (the argument types of its
+# entry points convert them).
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # the current stream's handle, without building a torch.cuda.Stream object for it
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ws(ws: torch.Tensor):
-    return ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(ws.numel() * ws.element_size())
+    return ws.data_ptr(), ws.nbytes
 
 
 # ---- the C entry points ------------------------------------------------------
