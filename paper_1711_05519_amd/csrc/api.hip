@@ -1656,10 +1656,12 @@ int rpca_materialize(const void* D, const rpca_params* p, const rpca_state* st, 
     if ((L_out && ldl < p->n) || (S_out && lds < p->n)) return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
-    RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, st->zeta, st->k, 1.0, 0)));
     const int K = p->r;
-    HIP_TRY(launch_convert(st->U, c.ws + c.L.off_AL, p->m * K, st->sigma, K, c.dtype, c.s));
-    HIP_TRY(launch_convert(st->V, c.ws + c.L.off_BL, p->n * K, nullptr, K, c.dtype, c.s));
+    ConvertArgs f;
+    f.add(st->U, c.ws + c.L.off_AL, p->m * K);
+    f.add(st->V, c.ws + c.L.off_BL, p->n * K);
+    f.scale = st->sigma;
+    if (L_out || S_out) HIP_TRY(launch_convert(f, K, c.dtype, c.s));
     MaterializeArgs a;
     a.D = D;
     a.ldd = p->ldd;
@@ -1667,7 +1669,7 @@ int rpca_materialize(const void* D, const rpca_params* p, const rpca_state* st, 
     a.n = (int)p->n;
     a.AL = c.ws + c.L.off_AL;
     a.BL = c.ws + c.L.off_BL;
-    a.ctrl = c.ctrl();
+    a.zeta = st->zeta;
     a.L_out = L_out;
     a.ldl = ldl;
     a.S_out = S_out;
@@ -1687,10 +1689,12 @@ int rpca_tangent_products(const void* D, const rpca_params* p, const double* A_L
     slot.give(&c);
     const int K = p->r;
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, zeta, 0, 1.0, 0)));
-    HIP_TRY(launch_convert(A_L, c.ws + c.L.off_AL, p->m * K, nullptr, K, c.dtype, c.s));
-    HIP_TRY(launch_convert(B_L, c.ws + c.L.off_BL, p->n * K, nullptr, K, c.dtype, c.s));
-    HIP_TRY(launch_convert(U_t, c.ws + c.L.off_Uf, p->m * K, nullptr, K, c.dtype, c.s));
-    HIP_TRY(launch_convert(V_t, c.ws + c.L.off_Vf, p->n * K, nullptr, K, c.dtype, c.s));
+    ConvertArgs f;
+    f.add(A_L, c.ws + c.L.off_AL, p->m * K);
+    f.add(B_L, c.ws + c.L.off_BL, p->n * K);
+    f.add(U_t, c.ws + c.L.off_Uf, p->m * K);
+    f.add(V_t, c.ws + c.L.off_Vf, p->n * K);
+    HIP_TRY(launch_convert(f, K, c.dtype, c.s));
     HIP_TRY(launch_cross(panel_args(c), K, c.dtype, c.s));   // AL^T U_f, BL^T V_f for the gather
     const Geo g = geo_for(c, K, true, c.mixed);
     RPCA_TRY(stream_launch(stream_args(c, D, BODY_ANY, g), K, c.dtype, true, c.mixed, c.s));

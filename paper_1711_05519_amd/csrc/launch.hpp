@@ -49,9 +49,24 @@ struct MaterializeArgs {
     int32_t m, n;
     const void* AL;
     const void* BL;
-    const Ctrl* ctrl;
+    double zeta;
     void* L_out; int64_t ldl;
     void* S_out; int64_t lds;
+};
+
+// Panels (FP64, K columns) copied in the passes' type by one launch.
+struct ConvertArgs {
+    int32_t n = 0;
+    const double* src[4];
+    void* dst[4];
+    int64_t count[4];
+    int32_t blocks[4];                // filled by the launcher
+    const double* scale = nullptr;    // factors of panel 0's columns, or null
+    void add(const double* s, void* d, int64_t c) {
+        src[n] = s;
+        dst[n] = d;
+        count[n++] = c;
+    }
 };
 
 // Panel-kernel arguments (one struct for all of them; unused fields ignored).
@@ -185,7 +200,6 @@ hipError_t launch_mlp_forward(const float* th, const float* phi, float* o, int B
 hipError_t launch_mlp_backward(const float* th, const float* phi, const float* g, int B, float* grad, hipStream_t s);
 hipError_t launch_mlp_adam(float* th, float* m, float* v, const float* g, int t, float lr, float b1, float b2,
                            float eps, hipStream_t s);
-hipError_t launch_convert(const double* src, void* dst, int64_t count, const double* scale, int K,
-                          int dtype, hipStream_t s);
+hipError_t launch_convert(ConvertArgs a, int K, int dtype, hipStream_t s);
 
 }  // namespace rpca

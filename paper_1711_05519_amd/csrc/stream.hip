@@ -455,10 +455,9 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
 
 template <typename T, int K, bool SOUT>
 __global__ __launch_bounds__(STREAM_THREADS) void k_materialize(
-    const T* __restrict__ D, const T* __restrict__ AL, const T* __restrict__ BL, const Ctrl* __restrict__ ctrl,
-    T* __restrict__ Lo, T* __restrict__ So, int64_t ldd, int64_t ldl, int64_t lds, int m, int n, int n_ct, int TM) {
+    const T* __restrict__ D, const T* __restrict__ AL, const T* __restrict__ BL, T zeta, T* __restrict__ Lo,
+    T* __restrict__ So, int64_t ldd, int64_t ldl, int64_t lds, int m, int n, int n_ct, int TM) {
     constexpr int VW = 16 / (int)sizeof(T);
-    const T zeta = static_cast<T>(ctrl->zeta);
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int ct = blockIdx.x % n_ct, rt = blockIdx.x / n_ct;
@@ -543,8 +542,8 @@ hipError_t materialize_dispatch(const MaterializeArgs& a, int K, hipStream_t s) 
 #define RPCA_CASE(KK) \
     case KK:                                                                                             \
         hipLaunchKernelGGL((k_materialize<T, KK, SOUT>), grid, block, 0, s, static_cast<const T*>(a.D),  \
-                           static_cast<const T*>(a.AL), static_cast<const T*>(a.BL), a.ctrl,             \
-                           static_cast<T*>(a.L_out), static_cast<T*>(a.S_out), a.ldd, a.ldl, a.lds, a.m, \
+                           static_cast<const T*>(a.AL), static_cast<const T*>(a.BL),                     \
+                           static_cast<T>(a.zeta), static_cast<T*>(a.L_out), static_cast<T*>(a.S_out), a.ldd, a.ldl, a.lds, a.m, \
                            a.n, n_ct, TM);                                                               \
         break;
         RPCA_CASE(1) RPCA_CASE(2) RPCA_CASE(3) RPCA_CASE(4) RPCA_CASE(5) RPCA_CASE(6)
