@@ -326,9 +326,9 @@ struct Layout {
     size_t total;
 };
 
-// The streaming pass runs one tile per resident workgroup (a single round, no
-// tail): the row tiling follows the kernel's occupancy on the device. The
-// workspace is sized for the largest tiling any device can ask for.
+// The streaming pass's row tiling follows the kernel's occupancy on the device
+// (stream_tiles). The workspace is sized for the largest tiling any device can
+// ask for: one tile per workgroup that could be resident.
 constexpr int STREAM_MAX_SLOTS = 2048;   // 256 CUs x 8 workgroups of 256 threads
 constexpr int STREAM_MIN_TM = 64;
 // Problems whose 64-row tiles would not give every CU a workgroup use tiles of
@@ -350,6 +350,36 @@ int n_rt_for(int m, int n_ct, int slots, bool fine_tiles) {
         if (cap < fine) cap = fine;
     }
     return n_rt < cap ? n_rt : cap;
+}
+
+// Row tiles for a pass whose 64-row tiles would be more than the `slots` resident
+// workgroups; per: tiles of a row of tiles, over all instances; at most cap. The
+// workgroups run in rounds of `slots`, and the last round takes as long as a full
+// one, so this takes, of the tilings that fill 1 to STREAM_MAX_ROUNDS rounds, the
+// one with the least rounds x (rows of a tile + STREAM_TILE_ROWS), the second the
+// rows that a tile's fixed cost is worth (panel rows into registers, closing sums,
+// one more partial for the gather). One round for single solves and at least two
+// for batches took: 24 x 2000 x 2000, r = 6, FP32 3.50 ms, now (one round instead
+// of two and three) 3.45; 20000 x 20000, r = 10, mixed 10.01 ms, now (the
+// initialisation's passes in two rounds, 98 % full, instead of one, 93 % full) 9.92.
+// 32, 128 and 256 in place of 64 are equal for the batch; 200 takes the other back.
+constexpr int STREAM_TILE_ROWS = 64;
+constexpr int STREAM_MAX_ROUNDS = 8;
+int stream_rounds(int m, int64_t per, int slots, int cap) {
+    int64_t best = INT64_MAX;
+    int n_rt = 1;
+    for (int rounds = 1; rounds <= STREAM_MAX_ROUNDS; ++rounds) {
+        const int64_t fit = (int64_t)rounds * slots / per;
+        if (fit < 1) continue;
+        const int t = fit < cap ? (int)fit : cap;
+        const int64_t cost = rounds * (int64_t)((m + t - 1) / t + STREAM_TILE_ROWS);
+        if (cost < best) {
+            best = cost;
+            n_rt = t;
+        }
+        if (t == cap) break;
+    }
+    return n_rt;
 }
 
 // batched: the layout of one instance of a batch: 64-row tiles and more (the
@@ -500,16 +530,11 @@ Geo geo_for(const Ctx& c, int K, bool rebuild, bool mx = false) {
     const int m = (int)c.p->m;
     const int occ = mx ? stream_mx_occupancy(K, rebuild) : stream_occupancy(K, c.dtype, rebuild);
     const int slots = occ * c.dev->cus;
-    int n_rt;
-    if (c.batch > 1) {
-        // a batch: at least two rounds of workgroups over all its instances, so
-        // that the last, partly filled round is a small part of the pass
-        const int64_t per = (int64_t)c.L.n_ct * c.batch;
-        const int want = (int)((2 * (int64_t)slots + per - 1) / per);
-        n_rt = n_rt_for(m, c.L.n_ct, want * c.L.n_ct, false);
-    } else {
-        n_rt = n_rt_for(m, c.L.n_ct, slots < STREAM_MAX_SLOTS ? slots : STREAM_MAX_SLOTS, c.dtype == RPCA_F64);
-    }
+    int n_rt = n_rt_for(m, c.L.n_ct, slots < STREAM_MAX_SLOTS ? slots : STREAM_MAX_SLOTS,
+                        c.dtype == RPCA_F64 && c.batch <= 1);
+    const int64_t per = (int64_t)c.L.n_ct * (c.batch > 1 ? c.batch : 1);
+    const int cap = (m + STREAM_MIN_TM - 1) / STREAM_MIN_TM;
+    if (per * cap > slots) n_rt = stream_rounds(m, per, slots, cap < c.L.n_rt_max ? cap : c.L.n_rt_max);
     if (n_rt > c.L.n_rt_max) n_rt = c.L.n_rt_max;
     int TM = (m + n_rt - 1) / n_rt;
     TM = (TM + STREAM_WAVES - 1) / STREAM_WAVES * STREAM_WAVES;
