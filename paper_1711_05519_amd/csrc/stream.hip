@@ -385,14 +385,33 @@ __global__ __launch_bounds__(STREAM_THREADS, (sizeof(T) == 4 && !REBUILD && K ==
 // accesses at any 4-byte address), so odd strides run the same code; lanes
 // past the last whole vector of a row go element by element.
 //
-// m = n = 10^4, r = 5, FP32, L and S (1.2 GB): 399 -> 244 us (4.9 TB/s; a plain
-// copy reaches 5.2); L alone 240 -> 81 us, where D is not read at all.
+// WHOLE: every row of the outputs starts at a multiple of MAT_SECTOR bytes, so
+// that a wave's 1 KB of a row is whole memory sectors: the outputs, which no
+// kernel reads back, are stored non-temporally. Otherwise neighbouring column
+// tiles share a sector at their edges: they go to the same XCD (xcd_tile) at about
+// the same time, through its L2, which puts the two halves together; beyond
+// MAT_FINE_KMAX columns half as many workgroups then are faster (what each loads
+// first, its rows of BL, is not whole sectors either).
+//
+// L and S, a call: m = n = 10^4, r = 5, FP32 (1.2 GB): 421 -> 251 us (the kernel
+// 4.9 TB/s; a plain copy reaches 5.2), FP64 640 -> 469. FP64, 10^4 x 3011, r = 1
+// (rows at any multiple of 8 bytes): 178 -> 173 us; 12000 x 2436, r = 9: 292 -> 182
+// (with twice the workgroups 188). 4096 workgroups took 254, 487, 179 and 182; the
+// ragged ones stored non-temporally, in plain order, 196 and 185.
+// L alone, 10^4 x 10^4, FP32: 240 -> 81 us, where D is not read at all.
 constexpr int MAT_U = 4;                           // rows in flight per wave
 constexpr int MAT_ROWS = MAT_U * STREAM_WAVES;     // rows of a workgroup per step
-constexpr int MAT_TILES = 4096;                    // workgroups aimed at (16 per CU)
+constexpr int MAT_TILES = 8192;                    // workgroups aimed at (32 per CU)
+constexpr int MAT_SECTOR = 64;
+constexpr int MAT_FINE_KMAX = 6;
+
+template <bool NT, typename V> __device__ __forceinline__ void mat_store(V v, V* p) {
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 
 // MAT_U rows i0, i0 + 4, ... of one wave; CHECK: some may lie at or past i_hi.
-template <typename T, int K, bool SOUT, bool CHECK>
+template <typename T, int K, bool SOUT, bool WHOLE, bool CHECK>
 __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_t ldd, const T* __restrict__ AL,
                                                  T* __restrict__ Lo, int64_t ldl, T* __restrict__ So, int64_t lds,
                                                  int i0, int i_hi, int j, int nv, T zeta,
@@ -407,7 +426,7 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
             if (CHECK && i >= i_hi) continue;
             const T* p = D + (size_t)i * ldd + j;
             if (nv == VW) {
-                d[u] = __builtin_nontemporal_load(reinterpret_cast<const VecT*>(p));
+                d[u] = *reinterpret_cast<const VecT*>(p);
             } else {
 #pragma unroll
                 for (int s = 0; s < VW; ++s) d[u][s] = s < nv ? p[s] : T(0);
@@ -433,7 +452,7 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
         if (Lo) {
             T* p = Lo + (size_t)i * ldl + j;
             if (nv == VW) {
-                __builtin_nontemporal_store(l, reinterpret_cast<VecT*>(p));
+                mat_store<WHOLE>(l, reinterpret_cast<VecT*>(p));
             } else {
 #pragma unroll
                 for (int s = 0; s < VW; ++s)
@@ -443,7 +462,7 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
         if constexpr (SOUT) {
             T* p = So + (size_t)i * lds + j;
             if (nv == VW) {
-                __builtin_nontemporal_store(o, reinterpret_cast<VecT*>(p));
+                mat_store<WHOLE>(o, reinterpret_cast<VecT*>(p));
             } else {
 #pragma unroll
                 for (int s = 0; s < VW; ++s)
@@ -453,14 +472,15 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
     }
 }
 
-template <typename T, int K, bool SOUT>
+template <typename T, int K, bool SOUT, bool WHOLE>
 __global__ __launch_bounds__(STREAM_THREADS) void k_materialize(
     const T* __restrict__ D, const T* __restrict__ AL, const T* __restrict__ BL, T zeta, T* __restrict__ Lo,
     T* __restrict__ So, int64_t ldd, int64_t ldl, int64_t lds, int m, int n, int n_ct, int TM) {
     constexpr int VW = 16 / (int)sizeof(T);
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int ct = blockIdx.x % n_ct, rt = blockIdx.x / n_ct;
+    const int tile = WHOLE ? blockIdx.x : xcd_tile(blockIdx.x, gridDim.x);
+    const int ct = tile % n_ct, rt = tile / n_ct;
     const int j = (ct * WAVE + lane) * VW;
     const int nv = min(max(n - j, 0), VW);
     if (nv == 0) return;
@@ -469,8 +489,8 @@ __global__ __launch_bounds__(STREAM_THREADS) void k_materialize(
     const int i_hi = min(m, (rt + 1) * TM);
     int i0 = rt * TM + wave;
     for (; i0 + STREAM_WAVES * (MAT_U - 1) < i_hi; i0 += MAT_ROWS)
-        materialize_rows<T, K, SOUT, false>(D, ldd, AL, Lo, ldl, So, lds, i0, i_hi, j, nv, zeta, b);
-    if (i0 < i_hi) materialize_rows<T, K, SOUT, true>(D, ldd, AL, Lo, ldl, So, lds, i0, i_hi, j, nv, zeta, b);
+        materialize_rows<T, K, SOUT, WHOLE, false>(D, ldd, AL, Lo, ldl, So, lds, i0, i_hi, j, nv, zeta, b);
+    if (i0 < i_hi) materialize_rows<T, K, SOUT, WHOLE, true>(D, ldd, AL, Lo, ldl, So, lds, i0, i_hi, j, nv, zeta, b);
 }
 
 // Read-bandwidth reference: every 16-byte word of [p, p + n16) read once,
@@ -527,12 +547,12 @@ hipError_t stream_dispatch(const StreamArgs& a, int K, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename T, bool SOUT>
-hipError_t materialize_dispatch(const MaterializeArgs& a, int K, hipStream_t s) {
+template <typename T, bool SOUT, bool WHOLE>
+hipError_t materialize_tiles(const MaterializeArgs& a, int K, hipStream_t s) {
     constexpr int TN = WAVE * (16 / (int)sizeof(T));
     const int n_ct = (a.n + TN - 1) / TN;
     const int most = (a.m + MAT_ROWS - 1) / MAT_ROWS;
-    int n_rt = MAT_TILES / n_ct;
+    int n_rt = (WHOLE || K <= MAT_FINE_KMAX ? MAT_TILES : MAT_TILES / 2) / n_ct;
     n_rt = n_rt < 1 ? 1 : (n_rt < most ? n_rt : most);
     int TM = (a.m + n_rt - 1) / n_rt;
     TM = (TM + MAT_ROWS - 1) / MAT_ROWS * MAT_ROWS;
@@ -540,11 +560,11 @@ hipError_t materialize_dispatch(const MaterializeArgs& a, int K, hipStream_t s) 
     const dim3 grid((unsigned)((int64_t)n_ct * n_rt)), block(STREAM_THREADS);
     switch (K) {
 #define RPCA_CASE(KK) \
-    case KK:                                                                                             \
-        hipLaunchKernelGGL((k_materialize<T, KK, SOUT>), grid, block, 0, s, static_cast<const T*>(a.D),  \
-                           static_cast<const T*>(a.AL), static_cast<const T*>(a.BL),                     \
-                           static_cast<T>(a.zeta), static_cast<T*>(a.L_out), static_cast<T*>(a.S_out), a.ldd, a.ldl, a.lds, a.m, \
-                           a.n, n_ct, TM);                                                               \
+    case KK:                                                                                                   \
+        hipLaunchKernelGGL((k_materialize<T, KK, SOUT, WHOLE>), grid, block, 0, s, static_cast<const T*>(a.D), \
+                           static_cast<const T*>(a.AL), static_cast<const T*>(a.BL), static_cast<T>(a.zeta),  \
+                           static_cast<T*>(a.L_out), static_cast<T*>(a.S_out), a.ldd, a.ldl, a.lds, a.m, a.n, \
+                           n_ct, TM);                                                                         \
         break;
         RPCA_CASE(1) RPCA_CASE(2) RPCA_CASE(3) RPCA_CASE(4) RPCA_CASE(5) RPCA_CASE(6)
         RPCA_CASE(7) RPCA_CASE(8) RPCA_CASE(9) RPCA_CASE(10) RPCA_CASE(11) RPCA_CASE(12)
@@ -553,6 +573,14 @@ hipError_t materialize_dispatch(const MaterializeArgs& a, int K, hipStream_t s) 
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <typename T, bool SOUT> hipError_t materialize_dispatch(const MaterializeArgs& a, int K, hipStream_t s) {
+    const auto whole = [](const void* p, int64_t ld) {
+        return !p || ((uintptr_t)p % MAT_SECTOR == 0 && (ld * (int64_t)sizeof(T)) % MAT_SECTOR == 0);
+    };
+    return whole(a.L_out, a.ldl) && whole(a.S_out, a.lds) ? materialize_tiles<T, SOUT, true>(a, K, s)
+                                                          : materialize_tiles<T, SOUT, false>(a, K, s);
 }
 
 template <typename T, bool REBUILD>
