@@ -35,7 +35,7 @@
 // Kernels: a pass over D per body and direction (recompute of Y1, Y2; then
 // Z N_V, Z^T N_U, the zeta derivative and the Hadamard products with the
 // previous body's bases), thin Grams summed in a fixed order, thin row
-// combinations out = [panels] S with S formed by single-wave FP64 tails, and
+// combinations out = [panels] S with S formed by FP64 tails, and
 // the row-local Trim steps. Everything but D is FP64.
 
 #include <math.h>

@@ -24,7 +24,7 @@ constexpr double JACOBI_QUAD = 1e-8;
 // take (about 4e-8) are below the rounding of those products (6e-8) and of the
 // FP32 factors the result is stored in, and below the initial subspace
 // iteration's FP32 tolerance (3e-6), so stopping here changes nothing the FP32
-// path can resolve. It saves about one sweep of the single-wave tail per body.
+// path can resolve. It saves about one sweep of the tail per body.
 constexpr double JACOBI_QUAD_F32 = 2e-4;
 constexpr double CHOL_DEAD_REL = 1e-26;
 
