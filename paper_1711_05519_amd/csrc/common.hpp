@@ -209,13 +209,11 @@ __device__ inline int xcd_tile(int b, int G) {
 
 // Loads of D, which every pass reads exactly once. NT: marked non-temporal, so
 // that streaming the m x n data does not evict from the L2 what the kernels
-// around the pass reuse (bases, partial sums, code). Measured at
-// m = n = 10^4, r = 5: FP32 loop pass 97.2 -> 95.6 us, initialisation pass
-// 98.2 -> 94.8 us, loop body 147.9 -> 144.2 us; at m = n = 2 10^4, r = 10,
-// where the pass is bound by its vector ALU work, the loop pass went from
-// 641 to 675 us, and FP64 passes (8-byte D) were slower with them at every
-// size measured (m = n = 5000: solve 2.09 -> 2.43 ms). Passes over FP32 D use
-// them for blocks of up to D_LOADS_NT_KMAX columns.
+// around the pass reuse (bases, partial sums, code). FP32 passes up to
+// D_LOADS_NT_KMAX columns: a learned solve at m = n = 10^4, r = 5, took
+// 1.64 ms with plain loads, 1.50 with these. Beyond, where the vector ALU work
+// bounds the pass, they made it 5 % slower (r = 10), as they did FP64 passes
+// (8-byte D) at every size measured (m = n = 5000: solve 2.09 -> 2.43 ms).
 constexpr int D_LOADS_NT_KMAX = 6;
 template <bool NT> __device__ inline float load_d(const float* p) {
     if constexpr (!NT) return *p;

@@ -280,10 +280,17 @@ __device__ __forceinline__ void stream_rows(
     }
 }
 
-// Waves per SIMD of the initialisation's FP32 pass at K = 15: the closing sums of an
-// update (pass_finishes_update) must not cost the pass one.
+// Waves per SIMD of the FP32 passes that miss three by a register or two: the
+// initialisation's at K = 15 (by the closing sums of an update) and the loop's at
+// K = 10 (169 of 168). The latter: 2 10^4 x 2 10^4, r = 10, plain schedule
+// 14.31 -> 11.72 ms, 10^4 x 10^4 4.52 -> 4.02. (At K = 11, 183, the bound spills:
+// 16000 x 16000 9.29 -> 10.93.)
+template <typename T, int K, bool REBUILD> constexpr int stream_min_waves() {
+    return sizeof(T) == 4 && K == (REBUILD ? 10 : 15) ? 3 : 1;
+}
+
 template <typename T, int K, bool REBUILD>
-__global__ __launch_bounds__(STREAM_THREADS, (sizeof(T) == 4 && !REBUILD && K == 15) ? 3 : 1) void k_stream(
+__global__ __launch_bounds__(STREAM_THREADS, (stream_min_waves<T, K, REBUILD>())) void k_stream(
     const T* __restrict__ D, const T* __restrict__ AL, const T* __restrict__ BL, const T* __restrict__ Uf,
     const T* __restrict__ Vf, typename AccOf<T>::type* __restrict__ P1, typename AccOf<T>::type* __restrict__ P2,
     double* __restrict__ resid, Ctrl* __restrict__ ctrl, StreamGeom g) {
