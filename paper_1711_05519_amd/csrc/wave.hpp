@@ -264,15 +264,16 @@ constexpr int pow2_floor(int x) { int p = 1; while (p * 2 <= x) p *= 2; return p
 //     cancellation is below the rounding of the largest column's square, where
 //     pairs are under the absolute floor.
 //   - The angle is found in FP32 (A is scaled by a power of two to a norm near
-//     1), tan(theta) good to about 2^-22; cosine and sine of that angle are formed
-//     from it in FP64, so the rotation is orthogonal to FP64 and only the
-//     coupling it leaves is that fraction of the one it found. A sweep already
-//     leaves the square of its angles, so what a sweep that ends the iteration
-//     leaves is 2^-22 of an angle below quad: rounding.
+//     1), tan(theta) good to about 2^-22, and refined by one Newton step in FP64,
+//     good to about 2^-44; cosine and sine are formed from it in FP64. Without
+//     that step a rotation leaves 2^-22 of its coupling phi sigma_i^2, which after a
+//     last sweep with angles phi near 1e-8 is 2^-22 phi sigma_i / sigma_j between the left
+//     vectors: orthogonality 1e-13 at sigma_i / sigma_j = 100, 1e-11 at 10^4.
 // With the columns in LDS, both matrices in one wave and FP64 angles a round took
 // 0.36 us at N = 12 and 0.55 at N = 22; now 0.24 and 0.33 (gather of the
 // initialisation at m = n = 10^4, 2K = 12: 39 -> 30 us; at 2 10^4, 2K = 22: 115 ->
-// 90 us; FP64 complement at n = 1000, 2K = 12: 32 -> 24 us).
+// 90 us; FP64 complement at n = 1000, 2K = 12: 32 -> 24 us). The Newton step's part of
+// such a launch is about 2 %: 26.8 -> 27.4 us, 89.1 -> 89.6 and 22.1 -> 23.6.
 //
 // jacobi_svd is called by every live wave of the workgroup with its index: wave 0
 // works on A, wave 1 on the right vectors, others only take part in the
@@ -391,8 +392,13 @@ __device__ __forceinline__ int jacobi_left(const double* A, double* sig, double*
                              ((al > floor_neg) | (be > floor_neg));
             const float tf = rot ? tn : 0.f;
             tmax = fmaxf(tmax, fabsf(tf));
+            // one Newton step in FP64 on ga t^2 + (be - al) t - ga = 0, whose derivative at the root is +- hyp
+            const double t0 = (double)tf;
+            const double dt = fma(be - al, t0, ga * fma(t0, t0, -1.0)) *
+                              (double)copysignf(__builtin_amdgcn_rcpf(hyp), dl);
+            const double tt = rot ? t0 - dt : 0.0;
             // c = 1 / sqrt(1 + tan^2) by one third-order step from the FP32 value, s = tan c
-            const double tt = (double)tf, q = fma(tt, tt, 1.0);
+            const double q = fma(tt, tt, 1.0);
             const double y = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.f));
             const double e = fma(-q * y, y, 1.0);
             const double c = fma(y * e, fma(0.375, e, 0.5), y), s = tt * c;
