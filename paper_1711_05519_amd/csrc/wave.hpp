@@ -438,12 +438,13 @@ __device__ __forceinline__ int jacobi_left(const double* A, double* sig, double*
     }
     wave_sync();
     if (lane < N) {
-        const double sj = J->norm[lane];
+        // (a NaN norm ranks as infinite: the ranks are a permutation, and every entry is written)
+        const double sj = J->norm[lane], kj = sj == sj ? sj : INFINITY;
         int rank = 0;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const double si = J->norm[i];
-            rank += (si > sj) || (si == sj && i < lane);
+            const double si = J->norm[i], ki = si == si ? si : INFINITY;
+            rank += (ki > kj) || (ki == kj && i < lane);
         }
         J->rank[lane] = rank;
         sig[rank] = ldexp(sj, sh);
