@@ -34,7 +34,10 @@
  *   overlap. Calls with distinct workspaces may run concurrently; at most 32
  *   rpca_init / rpca_solve calls may be in flight per device (each holds a
  *   small slot of host-visible status memory; beyond that they return
- *   RPCA_EHIP with rpca_last_hip_error() = hipErrorOutOfMemory).
+ *   RPCA_EHIP with rpca_last_hip_error() = hipErrorOutOfMemory). The other
+ *   calls that report results hold one of 32 further slots, or copy their
+ *   results when none is free: their number is not limited, and they never
+ *   take a solve's.
  * - Return value: RPCA_OK (0) or RPCA_MAXITER (1) on success, a negative
  *   RPCA_E* code on failure. Arguments are validated before any launch; a
  *   failed validation leaves every output untouched.

@@ -53,8 +53,14 @@ constexpr int MAX_DEVICES = 64;
     } while (0)
 
 // Status slots in mapped, coherent host memory, one per call in flight on a
-// device that runs a queue of bodies (rpca_init, rpca_solve).
-constexpr int STATUS_SLOTS = 32;
+// device. Calls that run a queue of bodies (rpca_init, rpca_solve) need one and
+// have SOLVE_SLOTS of their own; calls that only report results through one
+// (and copy them when none is free) share the others, so that they never take a
+// solve's.
+constexpr int SOLVE_SLOTS = 32;
+constexpr int REPORT_SLOTS = 32;
+constexpr int STATUS_SLOTS = SOLVE_SLOTS + REPORT_SLOTS;
+static_assert(STATUS_SLOTS <= 64, "one bit of DeviceInfo::slots_used each");
 
 constexpr int BATCH_BUFS = 4;
 struct BatchBuf {
@@ -71,7 +77,7 @@ struct DeviceInfo {
     int cus = 256;
     HostStatus* status_host = nullptr;   // STATUS_SLOTS slots, allocated by the first call that needs one
     HostStatus* status_dev = nullptr;
-    uint32_t slots_used = 0;             // bit i: slot i belongs to a call (g_dev_mutex)
+    uint64_t slots_used = 0;             // bit i: slot i belongs to a call (g_dev_mutex)
     void* scratch = nullptr;             // this device's copy of `scratch` (rpca_step_noalloc)
     // mapped host buffers of rpca_solve_batch, grown on demand and kept; a
     // batched call holds one (its mutex) while it runs, so up to BATCH_BUFS
@@ -124,15 +130,18 @@ bool status_slots_locked(DeviceInfo* d) {
 }
 
 // A status slot held for the duration of one call (none for a null device).
+enum SlotUse : int { SLOT_SOLVE = 0, SLOT_REPORT = 1 };
 class StatusSlot {
 public:
-    explicit StatusSlot(DeviceInfo* d) : d_(d) {
+    StatusSlot(DeviceInfo* d, SlotUse use) : d_(d) {
         if (!d_) return;
         std::lock_guard<std::mutex> lock(g_dev_mutex);
         if (!status_slots_locked(d_)) return;
-        for (int i = 0; i < STATUS_SLOTS; ++i) {
-            if (!(d_->slots_used & (1u << i))) {
-                d_->slots_used |= 1u << i;
+        const int first = use == SLOT_SOLVE ? 0 : SOLVE_SLOTS;
+        const int last = use == SLOT_SOLVE ? SOLVE_SLOTS : STATUS_SLOTS;
+        for (int i = first; i < last; ++i) {
+            if (!(d_->slots_used & ((uint64_t)1 << i))) {
+                d_->slots_used |= (uint64_t)1 << i;
                 idx_ = i;
                 memset(d_->status_host + i, 0, sizeof(HostStatus));
                 break;
@@ -142,7 +151,7 @@ public:
     ~StatusSlot() {
         if (idx_ < 0) return;
         std::lock_guard<std::mutex> lock(g_dev_mutex);
-        d_->slots_used &= ~(1u << idx_);
+        d_->slots_used &= ~((uint64_t)1 << idx_);
     }
     StatusSlot(const StatusSlot&) = delete;
     StatusSlot& operator=(const StatusSlot&) = delete;
@@ -164,7 +173,7 @@ private:
 bool is_fin(double x) { return isfinite(x) != 0; }
 
 #define RPCA_TAKE_SLOT(slot, c)                                       \
-    StatusSlot slot((c).dev);                                         \
+    StatusSlot slot((c).dev, SLOT_SOLVE);                             \
     if (!slot.ok()) {                                                 \
         g_last_hip_error = (int)hipErrorOutOfMemory;                  \
         return RPCA_EHIP;                                             \
@@ -979,7 +988,7 @@ public:
         if (!D || hist_cap < 0) return RPCA_EINVAL;
         RPCA_TRY(check_state(st));
         RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c_));
-        slot_.reset(new StatusSlot(c_.dev));
+        slot_.reset(new StatusSlot(c_.dev, SLOT_SOLVE));
         if (!slot_->ok()) {
             g_last_hip_error = (int)hipErrorOutOfMemory;
             return RPCA_EHIP;
@@ -1475,7 +1484,7 @@ int step_impl(const void* D, const rpca_params* p, rpca_state* st, void* ws, siz
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
     c.events = events;
-    StatusSlot slot(events ? c.dev : nullptr);
+    StatusSlot slot(events ? c.dev : nullptr, SLOT_REPORT);
     slot.give(&c);
     double nd2 = st->normD > 0 ? st->normD * st->normD : 0.0;
     if (!(nd2 > 0)) RPCA_TRY(compute_normD2(c, D, &nd2));
@@ -1522,7 +1531,7 @@ int rpca_relaxed_step(const void* D, const rpca_params* p, rpca_state* st, doubl
     if (!is_fin(zeta) || !(zeta > 0) || !is_fin(tau) || !(tau > 0)) return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
-    StatusSlot slot(c.dev);
+    StatusSlot slot(c.dev, SLOT_REPORT);
     slot.give(&c);
     double nd2 = st->normD > 0 ? st->normD * st->normD : 0.0;
     if (!(nd2 > 0)) RPCA_TRY(compute_normD2(c, D, &nd2));
@@ -1606,7 +1615,7 @@ int rpca_unrolled_adjoint(const void* D, const rpca_params* p, int32_t K, const 
             return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
-    StatusSlot slot(c.dev);
+    StatusSlot slot(c.dev, SLOT_REPORT);
     slot.give(&c);
     const Layout& L = c.L;
     AdjointBufs B;
@@ -1710,7 +1719,7 @@ int rpca_tangent_products(const void* D, const rpca_params* p, const double* A_L
     if (!D || !A_L || !B_L || !U_t || !V_t || !Y1 || !Y2 || !resid2 || isnan(zeta)) return RPCA_EINVAL;
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
-    StatusSlot slot(c.dev);
+    StatusSlot slot(c.dev, SLOT_REPORT);
     slot.give(&c);
     const int K = p->r;
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, zeta, 0, 1.0, 0)));
