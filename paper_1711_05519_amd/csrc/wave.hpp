@@ -37,11 +37,6 @@ __device__ inline void wave_sync() {
 }
 
 template <int K>
-__device__ inline void w_load(const double* __restrict__ g, double* s) {
-    for (int e = lane_id(); e < K * K; e += WAVE) s[e] = g[(e / K) * KMAX + (e % K)];
-    wave_sync();
-}
-template <int K>
 __device__ inline void w_store(const double* s, double* __restrict__ g) {
     for (int e = lane_id(); e < K * K; e += WAVE) g[(e / K) * KMAX + (e % K)] = s[e];
     wave_sync();
@@ -287,7 +282,7 @@ template <int N> struct JacobiGeom {
     static constexpr int NSUB = WAVE / PL;          // lanes per pair
     static constexpr int E = (N + NSUB - 1) / NSUB; // rows of a column per lane
 };
-enum JacobiFlag : int { JACOBI_GO = 0, JACOBI_LAST = 1, JACOBI_NONE = 2 };
+enum JacobiFlag : int { JACOBI_GO = 0, JACOBI_LAST = 1 };
 template <int N> struct JacobiLds {
     double cs[2][N - 1][JacobiGeom<N>::PL][2];      // the rotations of a sweep, two sweeps deep
     double norm[N];
@@ -481,7 +476,6 @@ template <int N> __device__ __forceinline__ void jacobi_right(double* Vo, Jacobi
     for (int sweep = 0;; ++sweep) {
         __syncthreads();
         const int flag = J->flag[sweep & 1];
-        if (flag == JACOBI_NONE) return;
 #pragma unroll 2
         for (int rd = 0; rd < N - 1; ++rd)
             jacobi_turn<N>(t, b, J->cs[sweep & 1][rd][pc][0], J->cs[sweep & 1][rd][pc][1], first, last);
@@ -499,12 +493,6 @@ template <int N> __device__ __forceinline__ void jacobi_right(double* Vo, Jacobi
             }
         }
     }
-    __syncthreads();
-}
-
-// Wave 0 of a workgroup whose wave 1 waits in jacobi_right: no SVD this time.
-template <int N> __device__ __forceinline__ void jacobi_none(JacobiLds<N>* J) {
-    if (lane_id() == 0) J->flag[0] = JACOBI_NONE;
     __syncthreads();
 }
 
