@@ -160,7 +160,7 @@ __device__ inline void load4(const T* __restrict__ p, int nvalid, T (&d)[4]) {
     }
 }
 
-template <typename T, int K> struct StreamCfg {
+template <typename T, int K, bool REBUILD> struct StreamCfg {
     // Rows per batch per wave. The batch's wave-uniform row data (2K values of
     // AL and Uf per row) live in scalar registers. The per-element cost of the
     // reduce-scatter depends on NB * K only weakly, while the registers of the
@@ -170,17 +170,20 @@ template <typename T, int K> struct StreamCfg {
     // 12, 16, 24, 32); from K = 6 on, where 16 is one or two rows, 24 hides more of
     // the latency than the wave it costs (24 instances of 2000 x 2000, K = 6 and 7:
     // 4.35 -> 4.22 ms; 2 10^4 x 2 10^4, initialisation at K = 11: 10.72 -> 10.45 ms).
+    // The loop pass at K = 11 keeps 16 (163 VGPRs, three waves; 183 and two with 24):
+    // 10^4 x 10^4 158 us a pass, 180 with 24; 2 10^4 x 2 10^4 595 and 717.
     // FP64 keeps 16 words: 24 and 32 were within the spread.
     static constexpr int WORDS = (int)(sizeof(T) / 4);
-    static constexpr int NB0 = (WORDS == 1 && K >= 6 ? 24 : 16) / (K * WORDS);
+    static constexpr bool DEEP = WORDS == 1 && K >= 6 && !(REBUILD && K == 11);
+    static constexpr int NB0 = (DEEP ? 24 : 16) / (K * WORDS);
     static constexpr int NB = NB0 < 1 ? 1 : (NB0 > 8 ? 8 : NB0);
 };
 
 // Loads rows i0, i0 + 4, ... of the wave's 4 columns.
-template <typename T, int K, bool FULL, bool CHECK>
+template <typename T, int K, bool REBUILD, bool FULL, bool CHECK>
 __device__ __forceinline__ void load_batch(const T* __restrict__ D, int64_t ldd, int i0, int i_hi, int jb,
-                                           int nvalid, T (&d)[StreamCfg<T, K>::NB][STREAM_CPL]) {
-    constexpr int NB = StreamCfg<T, K>::NB;
+                                           int nvalid, T (&d)[StreamCfg<T, K, REBUILD>::NB][STREAM_CPL]) {
+    constexpr int NB = StreamCfg<T, K, REBUILD>::NB;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int i = i0 + STREAM_WAVES * b;
@@ -196,11 +199,11 @@ __device__ __forceinline__ void load_batch(const T* __restrict__ D, int64_t ldd,
 // Threshold, residual and both product contributions of one loaded batch.
 template <typename T, int K, bool REBUILD, bool CHECK>
 __device__ __forceinline__ void compute_batch(
-    const T (&d)[StreamCfg<T, K>::NB][STREAM_CPL], const T* __restrict__ AL, const T* __restrict__ Uf,
+    const T (&d)[StreamCfg<T, K, REBUILD>::NB][STREAM_CPL], const T* __restrict__ AL, const T* __restrict__ Uf,
     int i0, int i_hi, T zeta, const T (&bl)[STREAM_CPL][K], const T (&vt)[STREAM_CPL][K],
     T (&y2)[STREAM_CPL][K], double& res, T& amax, typename AccOf<T>::type* __restrict__ P1t, int lane) {
     using Acc = typename AccOf<T>::type;
-    constexpr int NB = StreamCfg<T, K>::NB;
+    constexpr int NB = StreamCfg<T, K, REBUILD>::NB;
     T p[NB * K];
     T rs = T(0);
 #pragma unroll
@@ -254,12 +257,12 @@ __device__ __forceinline__ void stream_rows(
     int i_first, int i_hi, int jb, int nvalid, T zeta, const T (&bl)[STREAM_CPL][K],
     const T (&vt)[STREAM_CPL][K], T (&y2)[STREAM_CPL][K], double& res, T& amax,
     typename AccOf<T>::type* __restrict__ P1t, int lane) {
-    constexpr int NB = StreamCfg<T, K>::NB;
+    constexpr int NB = StreamCfg<T, K, REBUILD>::NB;
     constexpr int STEP = STREAM_WAVES * NB;
     int i0 = i_first;
     if (i0 + STREAM_WAVES * (NB - 1) < i_hi) {
         T cur[NB][STREAM_CPL], nxt[NB][STREAM_CPL];
-        load_batch<T, K, FULL, false>(D, ldd, i0, i_hi, jb, nvalid, nxt);
+        load_batch<T, K, REBUILD, FULL, false>(D, ldd, i0, i_hi, jb, nvalid, nxt);
         for (;;) {
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -267,7 +270,7 @@ __device__ __forceinline__ void stream_rows(
                 for (int s = 0; s < STREAM_CPL; ++s) cur[b][s] = nxt[b][s];
             const int i1 = i0 + STEP;
             const bool more = i1 + STREAM_WAVES * (NB - 1) < i_hi;
-            if (more) load_batch<T, K, FULL, false>(D, ldd, i1, i_hi, jb, nvalid, nxt);
+            if (more) load_batch<T, K, REBUILD, FULL, false>(D, ldd, i1, i_hi, jb, nvalid, nxt);
             compute_batch<T, K, REBUILD, false>(cur, AL, Uf, i0, i_hi, zeta, bl, vt, y2, res, amax, P1t, lane);
             i0 = i1;
             if (!more) break;
@@ -275,16 +278,16 @@ __device__ __forceinline__ void stream_rows(
     }
     for (; i0 < i_hi; i0 += STEP) {
         T cur[NB][STREAM_CPL];
-        load_batch<T, K, FULL, true>(D, ldd, i0, i_hi, jb, nvalid, cur);
+        load_batch<T, K, REBUILD, FULL, true>(D, ldd, i0, i_hi, jb, nvalid, cur);
         compute_batch<T, K, REBUILD, true>(cur, AL, Uf, i0, i_hi, zeta, bl, vt, y2, res, amax, P1t, lane);
     }
 }
 
-// Waves per SIMD of the FP32 passes that miss three by a register or two: the
-// initialisation's at K = 15 (by the closing sums of an update) and the loop's at
-// K = 10 (169 of 168). The latter: 2 10^4 x 2 10^4, r = 10, plain schedule
-// 14.31 -> 11.72 ms, 10^4 x 10^4 4.52 -> 4.02. (At K = 11, 183, the bound spills:
-// 16000 x 16000 9.29 -> 10.93.)
+// Waves per SIMD of the FP32 passes that miss three by a little: the
+// initialisation's at K = 15 and the loop's at K = 10 (169 VGPRs of 168). The
+// former, by the closing sums of an update, in whose Cholesky it spills 10 VGPRs
+// for it: 10^4 x 10^4 171 -> 153 us a pass, 2 10^4 x 2 10^4 645 -> 540. The latter:
+// 2 10^4 x 2 10^4, r = 10, plain schedule 14.31 -> 11.72 ms, 10^4 x 10^4 4.52 -> 4.02.
 template <typename T, int K, bool REBUILD> constexpr int stream_min_waves() {
     return sizeof(T) == 4 && K == (REBUILD ? 10 : 15) ? 3 : 1;
 }
