@@ -415,7 +415,9 @@ constexpr int MAT_TILES = 8192;                    // workgroups aimed at (32 pe
 constexpr int MAT_SECTOR = 64;
 constexpr int MAT_FINE_KMAX = 6;
 
-template <bool NT, typename V> __device__ __forceinline__ void mat_store(V v, V* p) {
+// (The vector type is named, not deduced: deduction drops its element alignment.)
+template <bool NT, typename T>
+__device__ __forceinline__ void mat_store(typename Vec16u<T>::type v, typename Vec16u<T>::type* p) {
     if constexpr (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
@@ -462,7 +464,7 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
         if (Lo) {
             T* p = Lo + (size_t)i * ldl + j;
             if (nv == VW) {
-                mat_store<WHOLE>(l, reinterpret_cast<VecT*>(p));
+                mat_store<WHOLE, T>(l, reinterpret_cast<VecT*>(p));
             } else {
 #pragma unroll
                 for (int s = 0; s < VW; ++s)
@@ -472,7 +474,7 @@ __device__ __forceinline__ void materialize_rows(const T* __restrict__ D, int64_
         if constexpr (SOUT) {
             T* p = So + (size_t)i * lds + j;
             if (nv == VW) {
-                mat_store<WHOLE>(o, reinterpret_cast<VecT*>(p));
+                mat_store<WHOLE, T>(o, reinterpret_cast<VecT*>(p));
             } else {
 #pragma unroll
                 for (int s = 0; s < VW; ++s)
