@@ -336,16 +336,18 @@ struct Layout {
 };
 
 // The streaming pass's row tiling follows the kernel's occupancy on the device
-// (stream_tiles). The workspace is sized for the largest tiling any device can
+// (geo_for). The workspace is sized for the largest tiling any device can
 // ask for: one tile per workgroup that could be resident.
 constexpr int STREAM_MAX_SLOTS = 2048;   // 256 CUs x 8 workgroups of 256 threads
 constexpr int STREAM_MIN_TM = 64;
 // Problems whose 64-row tiles would not give every CU a workgroup use tiles of
 // down to 16 rows (4 per wave) until they do. (Solves: FP64 300 x 200 r = 3, 5 -> 19
 // tiles, 12 -> 8 us a pass, 1135 -> 1021 us; FP64 1000 x 1000 r = 5, 64 -> 252 tiles, 16 -> 10 us,
-// 1543 -> 1442 us.) FP64 only: an FP32 solve stays on the tiles a batch of such
-// instances uses (finer ones would grow its memory), so that both sum in the
-// same order and keep the same entries above the thresholds.
+// 1543 -> 1442 us.) FP64 only: instances of a batch have memory for 64-row tiles
+// only, and an FP32 solve keeps those too, so that it sums in the order of a batch
+// that fits the resident workgroups; in another order entries at a threshold fall
+// on its other side. (A larger batch is tiled by stream_rounds, by its count, and
+// sums in an order of its own.)
 constexpr int STREAM_MIN_TM_SMALL = 16;
 constexpr int STREAM_SMALL_TILES = 256;
 
@@ -469,7 +471,7 @@ struct Ctx {
     int dtype;
     bool mixed;          // RPCA_FLAG_MIXED: BF16-product bodies while err_k >= mixed_err
     double mixed_err;
-    HostStatus* st_host = nullptr;   // the call's status slot (queues of bodies only)
+    HostStatus* st_host = nullptr;   // the call's status slot, if it has one
     HostStatus* st_dev = nullptr;
     mutable int32_t reports = 0;     // reports queued to the slot so far
     bool events = true;              // false: no profiler events (rpca_step_noalloc)
@@ -531,7 +533,8 @@ Ctrl base_ctrl(const Ctx& c, int stage, double zeta, int k, double normD2, int w
     return t;
 }
 
-// Row tiling of a streaming pass with block width K: one round of tiles.
+// Row tiling of a streaming pass with block width K: 64-row tiles (or finer ones,
+// STREAM_MIN_TM_SMALL) where the device holds them all at once, else stream_rounds.
 struct Geo {
     int TM, n_rt;
 };
@@ -1047,11 +1050,11 @@ public:
     bool queued_all() const { return queued_all_; }
     hipStream_t stream() const { return c_.s; }
 
-    // After the last body: waits for the stream, then fills the state and the
+    // After the last body: waits for its report, then fills the state and the
     // histories. Returns rpca_solve's status.
     int finish() {
         // the last kernel copies the control block and the histories' leading
-        // entries into the status slot: one synchronisation reads them all
+        // entries into the status slot: one wait reads them all
         if (rc_ >= 0) {
             const hipError_t le =
                 launch_publish(c_.ctrl(), c_.err_hist(), c_.zeta_hist(), p_->max_iter + 1, c_.st_dev, ++c_.reports, c_.s);

@@ -30,7 +30,7 @@ __host__ __device__ constexpr int gather_threads_for(int64_t m, int64_t n) {
 }
 constexpr int GPART_STRIDE = 2 * KMAX * KMAX;   // doubles per workgroup partial slot
 // relaxed iteration (threshold training)
-constexpr int RX_KMAX = 10;        // largest rank of the relaxed iteration (3r <= 30 for the wave SVD)
+constexpr int RX_KMAX = 10;        // largest rank of the relaxed iteration (3r columns of a combination, at most 32)
 constexpr int RX_TRUE_MAX = 16;    // largest rank of the loss's target factors
 constexpr int RX_THREADS = 256;    // columns per tile of its pass over D
 constexpr int RX_MAX_RT = 32;      // row tiles of that pass: 256 tiles, one per CU, at m = n = 2000

@@ -548,7 +548,7 @@ __global__ __launch_bounds__(NT) void k_gather(PanelArgs a_) {
         rows_outer_sum<K, RPB, NT>(f, y, writer, slot, sa, sb, gp);   // U_f^T Y1 or V_f^T Y2
     if (!last_block_arrives(&ctrl->cnt[CNT_GATHER], &flag)) return;
 
-    // ---- last workgroup: all threads sum the partials, then one wave ----
+    // ---- last workgroup: all threads sum the partials, then the tail's waves ----
     __shared__ double sums[4 * K * K], ru[K * K], rv[K * K], cs[K * K], c2[K * K], tmp[K * K], tmp2[K * K];
     __shared__ double g1[K * K], g2[K * K], tmp3[K * K], tmp4[K * K];
     __shared__ double part[NT], rsum[2];
@@ -1022,10 +1022,6 @@ __global__ void k_enter_loop(Ctrl* ctrl_, int64_t slab) {
     }
 }
 
-// End of a solve: copies the control block and the leading hist_n entries of
-// the err and zeta histories (at most k + 1 of them) into the call's status
-// slot in mapped host memory, so that the host reads them after one stream
-// synchronisation instead of three copies.
 // Ends a report to the host: everything this workgroup wrote to the slot is in
 // host memory before the count that the host waits for.
 __device__ inline void report_done(HostStatus* dst, int32_t count) {
@@ -1042,6 +1038,9 @@ __global__ void k_report(const double* src, int n, HostStatus* dst, int32_t coun
     report_done(dst, count);
 }
 
+// The control block and, at the end of a solve, the leading hist_n entries of the
+// err and zeta histories (at most k + 1 of them) into the status slot, where the
+// host polls for them: one wait instead of three copies.
 __global__ void k_publish(const Ctrl* ctrl, const double* err_hist, const double* zeta_hist, int hist_n,
                           HostStatus* dst, int32_t count) {
     constexpr int CW = (int)(sizeof(Ctrl) / 4);

@@ -1,7 +1,7 @@
 // Single-wave and whole-workgroup helpers of the small FP64 algebra: LDS
 // matrix moves, fixed-order sums of per-workgroup partials, a Cholesky
-// factorisation with inverse, and a one-sided Jacobi SVD run by two waves. Shared by the panel kernels of the loop and of the
-// relaxed iteration.
+// factorisation with inverse, and a one-sided Jacobi SVD run by two waves.
+// Shared by the panel kernels of the loop and of the relaxed iteration.
 #pragma once
 
 #include "launch.hpp"
@@ -255,9 +255,10 @@ constexpr int pow2_floor(int x) { int p = 1; while (p * 2 <= x) p *= 2; return p
 //     the cosines and sines left in LDS, one sweep behind (two buffers, one
 //     barrier per sweep).
 //   - Squared norms travel with their columns and are formed anew each sweep: a
-//     rotation changes them by +- tan(theta) (a_p . a_q). What that loses to
-//     cancellation is below the rounding of the largest column's square, where
-//     pairs are under the absolute floor.
+//     rotation changes them by +- tan(theta) (a_p . a_q). Within a sweep they are
+//     off by a few roundings of the largest column's square (about 1e-16 ||A||_F^2,
+//     more than the absolute floor), so a small column's angle can be wrong there;
+//     the next sweep starts from norms formed anew.
 //   - The angle is found in FP32 (A is scaled by a power of two to a norm near
 //     1), tan(theta) good to about 2^-22, and refined by one Newton step in FP64,
 //     good to about 2^-44; cosine and sine are formed from it in FP64. Without
