@@ -233,7 +233,8 @@ int rpca_solve_many(int32_t count, const void *const *D, const rpca_params *cons
  * aligned), laid out as rpca_batch_layout_of reports: its D (m x n, row stride
  * p->ldd, p->dtype) at off_D, filled by the caller; its iterate U (m x r), V
  * (n x r), sigma (r), FP64, at off_U, off_V, off_sigma, written by the call;
- * its workspace at off_ws. Each kernel launch covers all instances (grid y)
+ * its workspace at off_ws, of at least rpca_workspace_size bytes: it also serves
+ * the other calls on the instance. Each kernel launch covers all instances (grid y)
  * and each instance's control block gates its own work, so every instance
  * follows exactly the steps of rpca_solve (same stopping rule; with
  * RPCA_FLAG_MIXED every loop body takes BF16 products, so mixed_err must be

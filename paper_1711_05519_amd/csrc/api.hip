@@ -394,7 +394,7 @@ int stream_rounds(int m, int64_t per, int slots, int cap) {
 }
 
 // batched: the layout of one instance of a batch: 64-row tiles and more (the
-// instances fill the device), without the panels that no kernel of a batch uses.
+// instances fill the device).
 Layout make_layout(const rpca_params* p, bool batched = false) {
     Layout L;
     L.K_main = p->r;
@@ -421,10 +421,8 @@ Layout make_layout(const rpca_params* p, bool batched = false) {
     L.off_gpart = take(sizeof(double) * (size_t)(g_gather > L.gU + L.gV ? g_gather : L.gU + L.gV) * GPART_STRIDE);
     const size_t pm = sizeof(double) * (size_t)m * L.KW, pn = sizeof(double) * (size_t)n * L.KW;
     L.off_Y1 = take(pm); L.off_Y2 = take(pn);
-    // complements W (FP64 only) and the exact trimmed factors (rpca_trim only)
-    const bool has_w = !batched || p->dtype == RPCA_F64;
-    L.off_W1 = take(has_w ? pm : 0); L.off_W2 = take(has_w ? pn : 0);
-    L.off_Ap = take(batched ? 0 : pm); L.off_Bp = take(batched ? 0 : pn);
+    L.off_W1 = take(pm); L.off_W2 = take(pn);   // complements (FP64)
+    L.off_Ap = take(pm); L.off_Bp = take(pn);   // exact trimmed factors (rpca_trim)
     L.off_Unew = take(pm); L.off_Vnew = take(pn);
     const size_t tm = L.elt * (size_t)m * L.KW, tn = L.elt * (size_t)n * L.KW;
     L.off_Uf = take(tm); L.off_Vf = take(tn);
@@ -1259,7 +1257,10 @@ int rpca_batch_layout_of(const rpca_params* p, rpca_batch_layout* out) {
     out->off_U = take(sizeof(double) * (size_t)p->m * p->r);
     out->off_V = take(sizeof(double) * (size_t)p->n * p->r);
     out->off_sigma = take(sizeof(double) * p->r);
-    out->off_ws = take(L.total);
+    // a workspace for any call on the instance (rpca_materialize, rpca_step, ...),
+    // not for the batch alone
+    const size_t single = make_layout(p).total;
+    out->off_ws = take(L.total > single ? L.total : single);
     out->slab_bytes = off;
     return RPCA_OK;
 }
