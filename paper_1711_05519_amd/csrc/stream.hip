@@ -170,8 +170,12 @@ template <typename T, int K, bool REBUILD> struct StreamCfg {
     // 12, 16, 24, 32); from K = 6 on, where 16 is one or two rows, 24 hides more of
     // the latency than the wave it costs (24 instances of 2000 x 2000, K = 6 and 7:
     // 4.35 -> 4.22 ms; 2 10^4 x 2 10^4, initialisation at K = 11: 10.72 -> 10.45 ms).
-    // The loop pass at K = 11 keeps 16 (163 VGPRs, three waves; 183 and two with 24):
-    // 10^4 x 10^4 158 us a pass, 180 with 24; 2 10^4 x 2 10^4 595 and 717.
+    // A pass over 10^4 x 10^4 with 16 and 24, loop: K = 6 91 94, 7 102 110, 8 129 124, 9
+    // 139 130, 10 150 142, 11 157 180, 12 208 195 us; initialisation: 6 95 93, 7 97 99, 8 108
+    // 98, 9 111 104, 10 116 110, 11 128 115, 12 142 141; over 2999 x 1777 24 is as fast or up
+    // to 10 % faster at every K; from K = 13 on both are one row. So 24 but for the loop at
+    // K = 11 (163 VGPRs and three waves with 16, 183 and two with 24; 2 10^4 x 2 10^4 595
+    // and 717 us).
     // FP64 keeps 16 words: 24 and 32 were within the spread.
     static constexpr int WORDS = (int)(sizeof(T) / 4);
     static constexpr bool DEEP = WORDS == 1 && K >= 6 && !(REBUILD && K == 11);
