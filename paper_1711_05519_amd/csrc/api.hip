@@ -78,6 +78,7 @@ struct DeviceInfo {
     HostStatus* status_host = nullptr;   // STATUS_SLOTS slots, allocated by the first call that needs one
     HostStatus* status_dev = nullptr;
     uint64_t slots_used = 0;             // bit i: slot i belongs to a call (g_dev_mutex)
+    int32_t slots_owed[STATUS_SLOTS] = {};   // see StatusSlot (g_dev_mutex)
     void* scratch = nullptr;             // this device's copy of `scratch` (rpca_step_noalloc)
     // mapped host buffers of rpca_solve_batch, grown on demand and kept; a
     // batched call holds one (its mutex) while it runs, so up to BATCH_BUFS
@@ -130,6 +131,11 @@ bool status_slots_locked(DeviceInfo* d) {
 }
 
 // A status slot held for the duration of one call (none for a null device).
+//
+// A call whose wait fails (the stream cannot be asked while another one is captured
+// in global mode, say) can end with its last report still on the way. Its slot is
+// then owed that report and goes to no other call before it has arrived: its count
+// and values would pass for the other call's.
 enum SlotUse : int { SLOT_SOLVE = 0, SLOT_REPORT = 1 };
 class StatusSlot {
 public:
@@ -140,8 +146,13 @@ public:
         const int first = use == SLOT_SOLVE ? 0 : SOLVE_SLOTS;
         const int last = use == SLOT_SOLVE ? SOLVE_SLOTS : STATUS_SLOTS;
         for (int i = first; i < last; ++i) {
-            if (!(d_->slots_used & ((uint64_t)1 << i))) {
-                d_->slots_used |= (uint64_t)1 << i;
+            const uint64_t bit = (uint64_t)1 << i;
+            if ((d_->slots_used & bit) && d_->slots_owed[i] != 0 && published(i) == d_->slots_owed[i]) {
+                d_->slots_owed[i] = 0;
+                d_->slots_used &= ~bit;
+            }
+            if (!(d_->slots_used & bit)) {
+                d_->slots_used |= bit;
                 idx_ = i;
                 memset(d_->status_host + i, 0, sizeof(HostStatus));
                 break;
@@ -151,23 +162,35 @@ public:
     ~StatusSlot() {
         if (idx_ < 0) return;
         std::lock_guard<std::mutex> lock(g_dev_mutex);
-        d_->slots_used &= ~((uint64_t)1 << idx_);
+        if (reports_ && published(idx_) != *reports_) d_->slots_owed[idx_] = *reports_;
+        else d_->slots_used &= ~((uint64_t)1 << idx_);
     }
     StatusSlot(const StatusSlot&) = delete;
     StatusSlot& operator=(const StatusSlot&) = delete;
     bool ok() const { return idx_ >= 0; }
-    HostStatus* host() const { return d_->status_host + idx_; }
-    HostStatus* dev() const { return d_->status_dev + idx_; }
-    // for a call that can do without (its results are then copied)
-    template <typename C> void give(C* c) const {
+    // The slot for call c, which outlives it.
+    template <typename C> void give(C* c) {
+        c->st_host = d_->status_host + idx_;
+        c->st_dev = d_->status_dev + idx_;
+        reports_ = &c->reports;
+    }
+    // For a call that can do without (its results are then copied): if there is one
+    // and the stream is not being captured, where a report would never run.
+    template <typename C> void offer(C* c) {
         if (!ok()) return;
-        c->st_host = host();
-        c->st_dev = dev();
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->s, &capture) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (capture == hipStreamCaptureStatusNone) give(c);
     }
 
 private:
+    int32_t published(int i) const { return *const_cast<const volatile int32_t*>(&d_->status_host[i].published); }
     DeviceInfo* d_;
     int idx_ = -1;
+    const int32_t* reports_ = nullptr;   // reports that the call has queued
 };
 
 bool is_fin(double x) { return isfinite(x) != 0; }
@@ -178,8 +201,7 @@ bool is_fin(double x) { return isfinite(x) != 0; }
         g_last_hip_error = (int)hipErrorOutOfMemory;                  \
         return RPCA_EHIP;                                             \
     }                                                                 \
-    (c).st_host = slot.host();                                        \
-    (c).st_dev = slot.dev()
+    slot.give(&(c))
 
 // ---- measurement: events around every streaming pass ---------------------------
 struct Profiler {
@@ -764,7 +786,8 @@ int wait_report(const Ctx& c) {
 // slot; a call without one copies it).
 int read_ctrl(const Ctx& c, Ctrl* out) {
     if (c.st_host) {
-        HIP_TRY(launch_publish(c.ctrl(), nullptr, nullptr, 0, c.st_dev, ++c.reports, c.s));
+        HIP_TRY(launch_publish(c.ctrl(), nullptr, nullptr, 0, c.st_dev, c.reports + 1, c.s));
+        ++c.reports;
         RPCA_TRY(wait_report(c));
         memcpy(out, &c.st_host->fin, sizeof(Ctrl));
         return RPCA_OK;
@@ -777,7 +800,8 @@ int read_ctrl(const Ctx& c, Ctrl* out) {
 // n doubles in device memory (at most 2 PUBLISH_HIST), in the same way.
 int read_values(const Ctx& c, const double* src, int n, double* out) {
     if (c.st_host) {
-        HIP_TRY(launch_report(src, n, c.st_dev, ++c.reports, c.s));
+        HIP_TRY(launch_report(src, n, c.st_dev, c.reports + 1, c.s));
+        ++c.reports;
         RPCA_TRY(wait_report(c));
         memcpy(out, &c.st_host->hist[0][0], sizeof(double) * (size_t)n);
         return RPCA_OK;
@@ -994,8 +1018,7 @@ public:
             g_last_hip_error = (int)hipErrorOutOfMemory;
             return RPCA_EHIP;
         }
-        c_.st_host = slot_->host();
-        c_.st_dev = slot_->dev();
+        slot_->give(&c_);
         D_ = D;
         p_ = p;
         st_ = st;
@@ -1055,8 +1078,10 @@ public:
         // entries into the status slot: one wait reads them all
         if (rc_ >= 0) {
             const hipError_t le =
-                launch_publish(c_.ctrl(), c_.err_hist(), c_.zeta_hist(), p_->max_iter + 1, c_.st_dev, ++c_.reports, c_.s);
-            if (le != hipSuccess) {
+                launch_publish(c_.ctrl(), c_.err_hist(), c_.zeta_hist(), p_->max_iter + 1, c_.st_dev, c_.reports + 1, c_.s);
+            if (le == hipSuccess) {
+                ++c_.reports;
+            } else {
                 g_last_hip_error = (int)le;
                 rc_ = RPCA_EHIP;
             }
@@ -1489,7 +1514,7 @@ int step_impl(const void* D, const rpca_params* p, rpca_state* st, void* ws, siz
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
     c.events = events;
     StatusSlot slot(events ? c.dev : nullptr, SLOT_REPORT);
-    slot.give(&c);
+    slot.offer(&c);
     double nd2 = st->normD > 0 ? st->normD * st->normD : 0.0;
     if (!(nd2 > 0)) RPCA_TRY(compute_normD2(c, D, &nd2));
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, st->zeta, st->k, nd2, 0)));
@@ -1536,7 +1561,7 @@ int rpca_relaxed_step(const void* D, const rpca_params* p, rpca_state* st, doubl
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
     StatusSlot slot(c.dev, SLOT_REPORT);
-    slot.give(&c);
+    slot.offer(&c);
     double nd2 = st->normD > 0 ? st->normD * st->normD : 0.0;
     if (!(nd2 > 0)) RPCA_TRY(compute_normD2(c, D, &nd2));
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, zeta, st->k, nd2, 0)));
@@ -1620,7 +1645,7 @@ int rpca_unrolled_adjoint(const void* D, const rpca_params* p, int32_t K, const 
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
     StatusSlot slot(c.dev, SLOT_REPORT);
-    slot.give(&c);
+    slot.offer(&c);
     const Layout& L = c.L;
     AdjointBufs B;
     HIP_TRY(adjoint_carve(c.ws + L.off_adj, p->m, p->n, p->r, L.rx_nct, L.rx_nrt, &B));
@@ -1724,7 +1749,7 @@ int rpca_tangent_products(const void* D, const rpca_params* p, const double* A_L
     Ctx c;
     RPCA_TRY(make_ctx(p, ws, ws_bytes, stream, &c));
     StatusSlot slot(c.dev, SLOT_REPORT);
-    slot.give(&c);
+    slot.offer(&c);
     const int K = p->r;
     RPCA_TRY(setup(c, base_ctrl(c, STAGE_MAIN, zeta, 0, 1.0, 0)));
     ConvertArgs f;
